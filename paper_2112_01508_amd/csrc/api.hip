@@ -1,16 +1,17 @@
 // C ABI of libp3msr: argument checks, workspace, the launch pipeline, the
 // measure-and-keep autotuner and per-call counters.
 //
-// Pipeline of one force call (all on the caller's stream):
+// Pipeline of one force call, all on the caller's stream:
+//   fill      every cleared buffer of the call, the output among them
 //   keys      tile/subtile key per particle + rank inside its cell (atomics)
 //   scan      exclusive scan of the cell histogram -> cell_start
 //   scatter   particles into tile -> subtile order (section 2.1.3, memory
 //             reorder of "Other optimisations")
-//   flags     receiver flags per subset, scan, compaction
 //   fine      inside dense subtiles, particles reordered by fine sub-cell
-//   clusters  <= csize (8..64) consecutive receivers of one tile per cluster
-//   items     clusters split over their 27 neighbour tiles (work estimate)
-//   [read back the cluster and item totals: the only host synchronisation]
+//   receivers compacted per subset (skipped when every particle receives)
+//   plan      clusters of <= csize (8..64) consecutive receivers of one tile,
+//             and their work items over the neighbour tiles
+//   finish    the clusters' bounding boxes (and the adjoint's weights)
 //   pairs     one persistent launch over all items; an item's sums are stored
 //             (sole item of its cluster) or added with FP64 atomics
 #include <hip/hip_runtime.h>
@@ -94,13 +95,13 @@ struct TuneKey {
 // a slice of [base, base + size), handed out anew at each call (nothing is
 // freed or allocated); else each buffer grows with hipMalloc.
 struct SrWork {
-    DevBuf key, rank, cells, sp, perm, sel, sp2, perm2, sel2, flags, actpos, ncl, clusters,
-        itemcnt, items, bsum, counters, wa, scal, rp, rperm, rwa, fbig, msum, htab;
+    DevBuf key, rank, cells, sp, perm, sel, sp2, perm2, sel2, prefix, clusters, itemoff, items,
+        bsum, counters, wa, scal, rp, rperm, fbig, msum, htab;
     // deterministic mode: radix-sort keys and values (two of each), digit
     // counts, and the items' partial sums
     DevBuf det_k, det_v, det_hist, partials;
-    // single-pass scans: their tile status words and tile counters
-    DevBuf scan1;
+    // look-back launches: their tile status words and tile counters
+    DevBuf back;
     unsigned char *base = nullptr;
     size_t size = 0, used = 0;
 };
@@ -174,10 +175,8 @@ struct p3m_sr_context {
     int dbg_fail_after = -1;
     size_t alloc_bytes = 0;
     bool timed_last = false;
-    // start, pairs start, pairs end, end, sort end, sort end on the build
-    // stream (the dense subtiles' fine order)
-    hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    bool sort_b = false;   // ev[5] was recorded by the timed call
+    // start, pairs start, pairs end, end, sort end
+    hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     hipEvent_t tot_ev = nullptr;   // after the totals of a call reach host memory
     int *host_tot = nullptr;   // pinned: receivers, clusters, items of the current call
     // long-range PM workspace and timing
@@ -186,14 +185,6 @@ struct p3m_sr_context {
     // p3m_force: the long-range half runs on this stream beside the short range
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-    // build phase: the cluster boxes and the output clear run on this stream
-    // beside the item planning (forked from and joined to the call's stream)
-    hipStream_t bstream = nullptr;
-    hipEvent_t bfork = nullptr, bjoin = nullptr, bsort = nullptr, bsorted = nullptr;
-    // with every particle a receiver: the cluster and item planning runs on
-    // this stream beside the scatter and the fine order
-    hipStream_t pstream = nullptr;
-    hipEvent_t pfork = nullptr, pjoin = nullptr;
     p3m_lr_stats lr_stats{};
     bool lr_timed = false;
     hipStream_t lr_stream = nullptr;
@@ -620,7 +611,6 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     st.ms_build = st.ms_pairs = st.ms_total = st.ms_sort = -1.0f;
     h->last_stream = s;
     h->timed_last = false;
-    h->sort_b = false;
     if (h->timing) P3M_HIP(hipEventRecord(h->ev[0], s));
 
     const size_t out_elems = (size_t)n_sub * (size_t)n * 3;
@@ -632,12 +622,9 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     // ---- workspace (every buffer is taken before the first launch, apart
     // from the work items, whose count the device reports) ----
     w.used = 0;
-    const size_t nflags = (size_t)n * n_sub;
-    const size_t ncl_len = (size_t)n_sub * g.nt3;
-    const size_t cl_bound = ncl_len + (nflags + csize - 1) / csize;
+    const size_t rows = (size_t)n * n_sub;   // (subset, particle) rows
+    const size_t cl_bound = (size_t)n_sub * g.nt3 + (rows + csize - 1) / csize;
     const size_t det_hist = det ? stable_rank_hist_ints(n) : 0;
-    const size_t scan_max = std::max(std::max(std::max(ncells, nflags), std::max(ncl_len, cl_bound)),
-                                     det_hist);
     int rc;
     if ((rc = take(h, w, w.key, sizeof(int) * n, s))) return rc;
     if ((rc = take(h, w, w.rank, sizeof(int) * n, s))) return rc;
@@ -649,27 +636,24 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     if ((rc = take(h, w, w.sp2, sizeof(double4) * ((size_t)n + kSupplierPad), s))) return rc;
     if ((rc = take(h, w, w.perm2, sizeof(int) * n, s))) return rc;
     if ((rc = take(h, w, w.sel2, (size_t)n, s))) return rc;
-    if ((rc = take(h, w, w.flags, sizeof(int) * (nflags + 1), s))) return rc;
-    if ((rc = take(h, w, w.actpos, sizeof(int) * (nflags + 1), s))) return rc;
-    if ((rc = take(h, w, w.ncl, sizeof(int) * (ncl_len + 1), s))) return rc;
     if ((rc = take(h, w, w.clusters, sizeof(Cluster) * cl_bound, s))) return rc;
-    if ((rc = take(h, w, w.itemcnt, sizeof(int) * (cl_bound + 1), s))) return rc;
-    if ((rc = take(h, w, w.bsum, sizeof(int) * scan_block_sums_needed(scan_max), s))) return rc;
+    if ((rc = take(h, w, w.bsum, sizeof(int) * scan_block_sums_needed(std::max(ncells, det_hist)), s)))
+        return rc;
     if ((rc = take(h, w, w.counters, sizeof(Counters) * kCounterCopies * kCounterStride, s)))
         return rc;
-    if ((rc = take(h, w, w.scal, sizeof(int) * kXcds * kQueueStride, s))) return rc;
-    if ((rc = take(h, w, w.rp, sizeof(double4) * (nflags + 1), s))) return rc;
-    if ((rc = take(h, w, w.rperm, sizeof(int) * (nflags + 1), s))) return rc;
-    if (r.backward && (rc = take(h, w, w.rwa, sizeof(double4) * (nflags + 1), s))) return rc;
+    if ((rc = take(h, w, w.scal, sizeof(int) * (kXcds + 1) * kQueueStride, s))) return rc;
+    if (!all_recv) {
+        if ((rc = take(h, w, w.prefix, sizeof(int) * (rows + 1), s))) return rc;
+        if ((rc = take(h, w, w.rp, sizeof(double4) * (rows + 1), s))) return rc;
+        if ((rc = take(h, w, w.rperm, sizeof(int) * (rows + 1), s))) return rc;
+    }
     if (r.backward && (rc = take(h, w, w.wa, sizeof(double4) * ((size_t)n + kSupplierPad), s))) return rc;
     if (mutual && (rc = take(h, w, w.msum, sizeof(double) * 3 * (size_t)n, s))) return rc;
-    // the call's single-pass scans (cells, receiver flags, clusters, items)
-    const size_t s1_cells = scan1_status_needed(ncells);
-    const size_t s1_flags = all_recv ? 0 : scan1_status_needed(nflags);
-    const size_t s1_ncl = scan1_status_needed(ncl_len);
-    const size_t s1_items = scan1_status_needed(cl_bound);
-    const size_t s1_total = s1_cells + s1_flags + s1_ncl + s1_items;
-    if ((rc = take(h, w, w.scan1, sizeof(unsigned long long) * s1_total + 4 * sizeof(int), s)))
+    // the call's look-back launches (cell scan, receivers, plan)
+    const size_t back_cells = scan1_status_needed(ncells);
+    const size_t back_recv = all_recv ? 0 : receivers_status_needed(rows);
+    const size_t back_total = back_cells + back_recv + plan_status_needed(n_sub, g);
+    if ((rc = take(h, w, w.back, sizeof(unsigned long long) * back_total + 4 * sizeof(int), s)))
         return rc;
     if (det) {
         if ((rc = take(h, w, w.det_k, sizeof(unsigned long long) * 2 * (size_t)n, s))) return rc;
@@ -689,66 +673,42 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     if (!wait_count && w.base && w.used + item_bound * sizeof(Item) + 256 > w.size)
         wait_count = true;
     if (!wait_count && (rc = take(h, w, w.items, sizeof(Item) * item_bound, s))) return rc;
-    // With every particle a receiver the clusters and items follow from the
-    // cell counts alone (a cluster is a run of consecutive sorted particles
-    // of one subtile, whatever their order inside it): their planning runs
-    // on its own stream beside the scatter and the fine order, and only the
-    // cluster boxes, which read the final order, wait for both.
-    const bool early_plan = all_recv && !det && !wait_count;
+    if (wait_count && (rc = take(h, w, w.itemoff, sizeof(int) * (cl_bound + 1), s))) return rc;
 
     int *key = (int *)w.key.p, *rank = (int *)w.rank.p, *cells = (int *)w.cells.p;
     double4 *sp = (double4 *)w.sp.p;
     int *perm = (int *)w.perm.p;
     uint8_t *sel_s = (uint8_t *)w.sel.p;
-    int *flags = (int *)w.flags.p, *actpos = (int *)w.actpos.p, *ncl = (int *)w.ncl.p;
     Cluster *clusters = (Cluster *)w.clusters.p;
-    int *itemcnt = (int *)w.itemcnt.p, *bsum = (int *)w.bsum.p;
+    int *item_off = wait_count ? (int *)w.itemoff.p : nullptr;
     Counters *counters = (Counters *)w.counters.p;
     h->last_counters = counters;
-    int *scal = (int *)w.scal.p;   // the XCD work queues, kQueueStride ints apart
+    int *queue = (int *)w.scal.p;   // the XCD work queues, kQueueStride ints apart
+    int *n_clusters = queue + kXcds * kQueueStride, *n_items = n_clusters + 1;
 
     // ---- sort ----
     int *fbig = (int *)w.fbig.p;
-    int *queue = scal;
     double4 *sp_f = (double4 *)w.sp2.p;   // the sorted particles after the fine order
     {
-        // every small initialisation of the call in one launch
+        // everything the call clears, in one launch: the output too (the
+        // mutual kernel's sorted-order sums)
         FillSet f{};
         f.add(cells, ncells + 1, 0);
         f.add((int *)counters, sizeof(Counters) * kCounterCopies * kCounterStride / sizeof(int), 0);
         f.add(fbig, 1, 0);
         f.add(queue, kXcds * kQueueStride, 0);
         f.add((int *)(sp_f + n), kSupplierPad * sizeof(double4) / sizeof(int), 0);
-        if (all_recv) f.add(flags + nflags, 1, n);   // the receiver total
-        f.add((int *)w.scan1.p, 2 * s1_total + 4, 0);
+        f.add((int *)w.back.p, 2 * back_total + 4, 0);
+        if (mutual) f.add((int *)w.msum.p, 6 * (size_t)n, 0);
+        else f.add((int *)r.out, 2 * out_elems, 0);
         P3M_HIP(launch_fill_multi(f, s));
     }
-    unsigned long long *s1 = (unsigned long long *)w.scan1.p;
-    int *s1c = (int *)(s1 + s1_total);
+    unsigned long long *back = (unsigned long long *)w.back.p;
+    int *back_ctr = (int *)(back + back_total);
     unsigned long long *stall = &counters->scan_stall;
+    int *bsum = (int *)w.bsum.p;
     P3M_HIP(launch_keys(r.pos, n, g, key, rank, cells, s));
-    P3M_HIP(launch_scan1(cells, cells, ncells, s1, s1c, stall, bsum, s));
-    if (early_plan) {
-        P3M_HIP(hipEventRecord(h->pfork, s));
-        P3M_HIP(hipStreamWaitEvent(h->pstream, h->pfork, 0));
-        hipStream_t ps = h->pstream;
-        P3M_HIP(launch_cluster_count(cells, nullptr, n, n_sub, g, csize, ncl, ps));
-        P3M_HIP(launch_scan1(ncl, ncl, ncl_len, s1 + s1_cells + s1_flags, s1c + 2, stall, bsum, ps));
-        P3M_HIP(launch_cluster_write(cells, nullptr, ncl, n, n_sub, g, csize, clusters, ps));
-        P3M_HIP(launch_item_count(clusters, ncl + ncl_len, (int)cl_bound, cells, g, target,
-                                  mutual ? 1 : 0, itemcnt, ps));
-        P3M_HIP(launch_scan1(itemcnt, itemcnt, cl_bound, s1 + s1_cells + s1_flags + s1_ncl,
-                             s1c + 3, stall, bsum, ps));
-        P3M_HIP(launch_item_write(clusters, ncl + ncl_len, (int)cl_bound, cells, g, target,
-                                  mutual ? 1 : 0, itemcnt, (Item *)w.items.p, flags + nflags,
-                                  itemcnt + cl_bound, h->host_tot, ps));
-        if (shape != SHAPE_POLY)
-            P3M_HIP(launch_build_htab(shape, h->cfg_tab_n, g, (float *)w.htab.p, ps));
-        P3M_HIP(hipEventRecord(h->pjoin, ps));
-        // the dense subtiles' list needs only the cell counts as well
-        P3M_HIP(hipStreamWaitEvent(h->bstream, h->pfork, 0));
-        P3M_HIP(launch_big_list(cells, g, fbig, h->bstream));
-    }
+    P3M_HIP(launch_scan1(cells, cells, ncells, back, back_ctr, stall, bsum, s));
     if (det) {
         // ranks in (fine sub-cell, index) order instead of the atomics' order
         unsigned long long *k64 = (unsigned long long *)w.det_k.p;
@@ -764,34 +724,13 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
         // the later kernels then take every particle as active
         if (!sel_src) sel_s = sel_f = nullptr;
         P3M_HIP(launch_scatter(r.pos, r.mass, sel_src, n, g, key, rank, cells, fp32 ? 1 : 0,
-                               csize, det, sp, perm, sel_s, sp_f, perm_f, sel_f, s));
-        // fine order inside dense subtiles (key/rank are free again as scratch)
-        // a subtile no larger than one cluster gains nothing from the reorder;
-        // the stable ranks are in fine order already.  The subtiles above
-        // kFineBig particles are ordered on the build stream meanwhile (the
-        // box kernel needs both orders).
-        if (!det) {
-            if (!early_plan) P3M_HIP(launch_big_list(cells, g, fbig, s));
-            P3M_HIP(hipEventRecord(h->bsort, s));
-            P3M_HIP(hipStreamWaitEvent(h->bstream, h->bsort, 0));
-            P3M_HIP(launch_fine_order_big(sp, perm, sel_s, cells, g, key, rank, sp_f, perm_f,
-                                          sel_f, n, fbig, h->bstream));
-            if (h->timing) P3M_HIP(hipEventRecord(h->ev[5], h->bstream));
-            h->sort_b = h->timing;
-            // the receiver flags read the final selectors, the dense
-            // subtiles' among them: with flags the call's stream waits here
-            if (!all_recv) P3M_HIP(hipEventRecord(h->bsorted, h->bstream));
-            // the output (the mutual kernel: its sorted-order sums) is cleared
-            // on the build stream meanwhile; nothing before the pair kernel
-            // reads it
-            if (mutual) P3M_HIP(launch_fill_f64((double *)w.msum.p, 0.0, 3 * (size_t)n, h->bstream));
-            else P3M_HIP(launch_fill_f64(r.out, 0.0, out_elems, h->bstream));
-            // with the early planning the cluster boxes wait here: they read
-            // the final order (and the pair kernel the cleared output)
-            if (early_plan) P3M_HIP(hipEventRecord(h->bsorted, h->bstream));
-            P3M_HIP(launch_fine_order_medium(sp, perm, sel_s, cells, g, key, rank, sp_f, perm_f,
-                                             sel_f, csize, s));
-        }
+                               csize, det, sp, perm, sel_s, sp_f, perm_f, sel_f, fbig, s));
+        // fine order inside dense subtiles (key/rank are free again as
+        // scratch); a subtile no larger than one cluster gains nothing from
+        // the reorder, and the stable ranks are in fine order already
+        if (!det)
+            P3M_HIP(launch_fine_order(sp, perm, sel_s, cells, g, key, rank, sp_f, perm_f, sel_f, n,
+                                      csize, fbig, s));
         sp = sp_f;
         perm = perm_f;
         sel_s = sel_f;
@@ -800,96 +739,70 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
 
     // ---- receivers -> clusters -> items ----
     // the adjoint needs every particle as a receiver (its output rows are
-    // the particles near any active one); activity enters through wa
-    const int kind = r.backward ? SEL_ALL : r.sel_kind;
-    const int *recv_scan = flags, *recv_pos = actpos;
+    // the particles near any active one); activity enters through wa.  With
+    // every particle a receiver the receivers are sp / perm / wa as they are.
+    const double4 *rp = sp;
+    const int *rperm = perm;
+    if (!all_recv) {
+        P3M_HIP(launch_receivers(sel_s, n, n_sub, r.sel_kind, r.thr, sp, perm, (int *)w.prefix.p,
+                                 (double4 *)w.rp.p, (int *)w.rperm.p, back + back_cells,
+                                 back_ctr + 1, stall, s));
+        rp = (const double4 *)w.rp.p;
+        rperm = (const int *)w.rperm.p;
+    }
     double4 *wa = r.backward ? (double4 *)w.wa.p : nullptr;
     // receivers, clusters and items reach the stats when they are asked for
     st.receivers = st.clusters = st.items = -1;
-    if (early_plan) {
-        // the clusters and items are planned on their own stream already;
-        // the boxes wait for both halves of the fine order and for the
-        // planning, which is then also done before the pair kernel
-        P3M_HIP(hipStreamWaitEvent(s, h->bsorted, 0));
-        P3M_HIP(hipStreamWaitEvent(s, h->pjoin, 0));
-        if (r.backward) P3M_HIP(launch_gather_weights(r.grad_acc, sel_s, perm, n, fp32, wa, s));
-        P3M_HIP(launch_cluster_finish(clusters, ncl + ncl_len, cl_bound, csize, nullptr, sp, perm,
-                                      wa, nullptr, nullptr, nullptr, s));
-    } else {
-        if (all_recv) {
-            recv_scan = recv_pos = nullptr;
-        } else {
-            if (!det) P3M_HIP(hipStreamWaitEvent(s, h->bsorted, 0));
-            P3M_HIP(launch_flags(sel_s, n, n_sub, kind, r.thr, flags, s));
-            P3M_HIP(launch_scan1(flags, flags, nflags, s1 + s1_cells, s1c + 1, stall, bsum, s));
-            P3M_HIP(launch_compact(flags, n, n_sub, actpos, s));
-        }
-        P3M_HIP(launch_cluster_count(cells, recv_scan, n, n_sub, g, csize, ncl, s));
-        P3M_HIP(launch_scan1(ncl, ncl, ncl_len, s1 + s1_cells + s1_flags, s1c + 2, stall, bsum, s));
-        P3M_HIP(launch_cluster_write(cells, recv_scan, ncl, n, n_sub, g, csize, clusters, s));
-
-        // The cluster boxes, the receiver gather, the table (and in the
-        // deterministic mode the output clear) need neither each other's
-        // results nor the item planning: they run on the build stream beside
-        // it, joined before the pair kernel.  (The box kernel writes only the
-        // boxes of the cluster records, the item kernels read only the other
-        // fields.)
-        P3M_HIP(hipEventRecord(h->bfork, s));
-        P3M_HIP(hipStreamWaitEvent(h->bstream, h->bfork, 0));
-        hipStream_t bs = h->bstream;
-        if (r.backward) P3M_HIP(launch_gather_weights(r.grad_acc, sel_s, perm, n, fp32, wa, bs));
-        // with every particle a receiver the receivers are sp / perm / wa as they are
-        double4 *rp = all_recv ? nullptr : (double4 *)w.rp.p;
-        P3M_HIP(launch_cluster_finish(clusters, ncl + ncl_len, cl_bound, csize, recv_pos, sp, perm,
-                                      wa, rp, (int *)w.rperm.p,
-                                      r.backward ? (double4 *)w.rwa.p : nullptr, bs));
-        // the output is cleared here in the deterministic mode (which has no
-        // mutual kernel), else on the build stream beside the fine order
-        if (det) P3M_HIP(launch_fill_f64(r.out, 0.0, out_elems, bs));
-        if (shape != SHAPE_POLY)
-            P3M_HIP(launch_build_htab(shape, h->cfg_tab_n, g, (float *)w.htab.p, bs));
-        P3M_HIP(hipEventRecord(h->bjoin, bs));
-
-        P3M_HIP(launch_item_count(clusters, ncl + ncl_len, (int)cl_bound, cells, g, target,
-                                  mutual ? 1 : 0, itemcnt, s));
-        P3M_HIP(launch_scan1(itemcnt, itemcnt, cl_bound, s1 + s1_cells + s1_flags + s1_ncl,
-                             s1c + 3, stall, bsum, s));
-        // the three totals go to pinned memory for the stats: here when the
-        // call waits for the item count, else from the item writer
-        if (wait_count) {
-            P3M_HIP(launch_totals(flags + nflags, ncl + ncl_len, itemcnt + cl_bound, h->host_tot,
-                                  s));
-            P3M_HIP(hipEventRecord(h->tot_ev, s));
-            P3M_HIP(hipEventSynchronize(h->tot_ev));
-            const size_t n_items = (size_t)std::max(h->host_tot[2], 1);
-            if ((rc = take(h, w, w.items, sizeof(Item) * n_items, s))) return rc;
-            if (det &&
-                (rc = take(h, w, w.partials, sizeof(double) * 3 * (size_t)csize * n_items, s)))
-                return rc;
-        }
-        // the totals for the stats (already there when the call waited for them)
-        P3M_HIP(launch_item_write(clusters, ncl + ncl_len, (int)cl_bound, cells, g, target,
-                                  mutual ? 1 : 0, itemcnt, (Item *)w.items.p, flags + nflags,
-                                  itemcnt + cl_bound, wait_count ? nullptr : h->host_tot, s));
-        P3M_HIP(hipStreamWaitEvent(s, h->bjoin, 0));
+    {
+        PlanArgs pa{};
+        pa.cell_start = cells;
+        pa.prefix = all_recv ? nullptr : (const int *)w.prefix.p;
+        pa.n = n;
+        pa.n_sub = n_sub;
+        pa.csize = csize;
+        pa.target = target;
+        pa.half = mutual ? 1 : 0;
+        pa.clusters = clusters;
+        pa.items = wait_count ? nullptr : (Item *)w.items.p;
+        pa.item_off = item_off;
+        pa.status = back + back_cells + back_recv;
+        pa.ctr = back_ctr + 2;
+        pa.stall = stall;
+        pa.n_clusters = n_clusters;
+        pa.n_items = n_items;
+        pa.host_tot = h->host_tot;
+        P3M_HIP(launch_plan(pa, g, s));
     }
+    if (wait_count) {
+        P3M_HIP(hipEventRecord(h->tot_ev, s));
+        P3M_HIP(hipEventSynchronize(h->tot_ev));
+        const size_t count = (size_t)std::max(h->host_tot[2], 1);
+        if ((rc = take(h, w, w.items, sizeof(Item) * count, s))) return rc;
+        if (det && (rc = take(h, w, w.partials, sizeof(double) * 3 * (size_t)csize * count, s)))
+            return rc;
+        P3M_HIP(launch_item_write(clusters, n_clusters, (int)cl_bound, cells, g, target,
+                                  mutual ? 1 : 0, item_off, (Item *)w.items.p, s));
+    }
+    P3M_HIP(launch_cluster_finish(clusters, n_clusters, cl_bound, csize, rp, r.grad_acc, sel_s, perm,
+                                  fp32 ? 1 : 0, wa, s));
+    if (shape != SHAPE_POLY)
+        P3M_HIP(launch_build_htab(shape, h->cfg_tab_n, g, (float *)w.htab.p, s));
     Item *items = (Item *)w.items.p;
 
     // ---- pairs ----
     PairArgs a{};
     a.sp = sp;
-    a.rp = all_recv ? sp : (const double4 *)w.rp.p;
-    a.rwa = all_recv ? wa : (const double4 *)w.rwa.p;
+    a.rp = rp;
     a.cell_start = cells;
     a.clusters = clusters;
     a.items = items;
     a.wa = wa;
     a.queue = queue;
-    a.rperm = all_recv ? perm : (const int *)w.rperm.p;
+    a.rperm = rperm;
     a.out = r.out;
     a.out_stride = 3ll * n;
     a.counters = counters;
-    a.n_items_dev = itemcnt + cl_bound;
+    a.n_items_dev = n_items;
     a.partials = det ? (double *)w.partials.p : nullptr;
     a.unit_mass = r.mass ? 0 : 1;
     a.csize = csize;
@@ -929,7 +842,7 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     else P3M_HIP(launch_pairs(mode, screen, shape, a, (int)grid, s));
     if (mutual) P3M_HIP(launch_mutual_out((const double *)w.msum.p, perm, n, r.out, s));
     if (det)
-        P3M_HIP(launch_item_reduce(clusters, ncl + ncl_len, (int)cl_bound, itemcnt, a.partials,
+        P3M_HIP(launch_item_reduce(clusters, n_clusters, (int)cl_bound, item_off, a.partials,
                                    csize, a.rperm, r.out, a.out_stride, s));
     if (h->timing) {
         P3M_HIP(hipEventRecord(h->ev[2], s));
@@ -1065,14 +978,6 @@ int p3m_sr_create(p3m_sr_handle *out, int device) {
     // the events every call may record (timing, the totals' arrival)
     bool ev_ok = hipEventCreateWithFlags(&h->tot_ev, hipEventDisableTiming) == hipSuccess;
     for (hipEvent_t &e : h->ev) ev_ok = ev_ok && hipEventCreate(&e) == hipSuccess;
-    ev_ok = ev_ok && hipEventCreateWithFlags(&h->bfork, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&h->bsort, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&h->bsorted, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&h->bjoin, hipEventDisableTiming) == hipSuccess &&
-            hipStreamCreateWithFlags(&h->bstream, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&h->pfork, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&h->pjoin, hipEventDisableTiming) == hipSuccess &&
-            hipStreamCreateWithFlags(&h->pstream, hipStreamNonBlocking) == hipSuccess;
     if (!ev_ok) {
         (void)hipGetLastError();
         p3m_sr_destroy(h);
@@ -1087,12 +992,12 @@ int p3m_sr_destroy(p3m_sr_handle h) {
     (void)hipSetDevice(h->device);
     (void)hipDeviceSynchronize();
     SrWork &w = h->work;
-    DevBuf *bufs[] = {&w.key,     &w.rank,     &w.cells,    &w.sp,      &w.perm,
-                      &w.sel,     &w.sp2,      &w.perm2,    &w.sel2,    &w.flags,
-                      &w.actpos,  &w.ncl,      &w.clusters, &w.itemcnt, &w.items,
-                      &w.bsum,    &w.counters, &w.wa,       &w.scal,    &w.rp,
-                      &w.rperm,   &w.rwa,      &w.fbig,     &w.msum,    &w.htab,
-                      &w.det_k,   &w.det_v,    &w.det_hist, &w.partials, &w.scan1,
+    DevBuf *bufs[] = {&w.key,     &w.rank,    &w.cells,    &w.sp,       &w.perm,
+                      &w.sel,     &w.sp2,     &w.perm2,    &w.sel2,     &w.prefix,
+                      &w.clusters, &w.itemoff, &w.items,   &w.bsum,     &w.counters,
+                      &w.wa,      &w.scal,    &w.rp,       &w.rperm,    &w.fbig,
+                      &w.msum,    &w.htab,    &w.det_k,    &w.det_v,    &w.det_hist,
+                      &w.partials, &w.back,
                       &h->pm_real, &h->pm_spec, &h->pm_tab, &h->pm_key,  &h->pm_rank,
                       &h->pm_cnt,  &h->pm_rec,  &h->pm_nkey, &h->pm_perm, &h->pm_recv,
                       &h->kdk_acc, &h->kdk_lr,  &h->kdk_tq,  &h->kdk_tnext, &h->kdk_due,
@@ -1108,14 +1013,6 @@ int p3m_sr_destroy(p3m_sr_handle h) {
     if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
     if (h->join_ev) (void)hipEventDestroy(h->join_ev);
     if (h->aux) (void)hipStreamDestroy(h->aux);
-    if (h->bfork) (void)hipEventDestroy(h->bfork);
-    if (h->bsort) (void)hipEventDestroy(h->bsort);
-    if (h->bsorted) (void)hipEventDestroy(h->bsorted);
-    if (h->bjoin) (void)hipEventDestroy(h->bjoin);
-    if (h->bstream) (void)hipStreamDestroy(h->bstream);
-    if (h->pfork) (void)hipEventDestroy(h->pfork);
-    if (h->pjoin) (void)hipEventDestroy(h->pjoin);
-    if (h->pstream) (void)hipStreamDestroy(h->pstream);
     delete h;
     return P3M_OK;
 }
@@ -1652,7 +1549,7 @@ int p3m_sr_get_stats(p3m_sr_handle h, p3m_sr_stats *out) {
     if ((rc = set_device(h))) return rc;
     p3m_sr_stats st = h->stats;
     if (st.n > 0 && st.items < 0) {
-        // the totals of the latest run of the call (k_totals writes them to
+        // the totals of the latest run of the call (the plan writes them to
         // pinned memory; a graph replay of the call writes them again)
         P3M_HIP(hipStreamSynchronize(h->last_stream));
         st.receivers = h->host_tot[0];
@@ -1689,12 +1586,6 @@ int p3m_sr_get_stats(p3m_sr_handle h, p3m_sr_stats *out) {
         P3M_HIP(hipEventElapsedTime(&b, h->ev[1], h->ev[2]));
         P3M_HIP(hipEventElapsedTime(&t, h->ev[0], h->ev[3]));
         P3M_HIP(hipEventElapsedTime(&st.ms_sort, h->ev[0], h->ev[4]));
-        if (h->sort_b) {
-            float sb = 0;
-            P3M_HIP(hipEventSynchronize(h->ev[5]));
-            P3M_HIP(hipEventElapsedTime(&sb, h->ev[0], h->ev[5]));
-            st.ms_sort = std::max(st.ms_sort, sb);
-        }
         st.ms_build = a;
         st.ms_pairs = b;
         st.ms_total = t;

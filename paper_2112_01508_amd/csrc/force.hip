@@ -879,13 +879,13 @@ void k_pairs(PairArgs a) {
             ax = b.ax; ay = b.ay; az = b.az;
         } else if constexpr (MODE == BWD_F64) {
             BwdF64<SOFT> b;
-            const double4 w = a.rwa[cl.begin + il];
+            const double4 w = a.wa[cl.begin + il];
             b.wkx = w.x; b.wky = w.y; b.wkz = w.z; b.muk = xp.w;
             visit_item<SG, CAP>(b, item, cl, c, a, wc, list, wlist);
             ax = b.ax; ay = b.ay; az = b.az;
         } else {
             BwdF32<SOFT> b;
-            const float4 w = reinterpret_cast<const float4 *>(a.rwa)[cl.begin + il];
+            const float4 w = reinterpret_cast<const float4 *>(a.wa)[cl.begin + il];
             b.wkx = w.x; b.wky = w.y; b.wkz = w.z; b.muk = mu_f32(xp.w);
             visit_item<SG, CAP>(b, item, cl, c, a, wc, list, wlist);
             ax = b.ax; ay = b.ay; az = b.az;

@@ -8,7 +8,7 @@
 //   sel[p]       receiver selector of sorted particle p (active flag or rung)
 //   cell_start[c] first sorted index of fine cell c (c = tile*ns^3 + subtile),
 //                cell_start[ncells] = n
-//   act_pos[]    sorted indices of the receivers, subset-major, tile order
+//   rp[], rperm[] receivers (record, original index), subset-major, tile order
 //   clusters[]   receiver groups of <= csize (8..64) particles inside one tile
 //   items[]      (cluster, neighbour-tile range, subtile range) work units,
 //                the items of one cluster consecutive
@@ -33,7 +33,7 @@ constexpr int kFineSide = 8;                // fine order: 8x8x8 sub-cells per s
 constexpr int kFineBins = kFineSide * kFineSide * kFineSide;
 constexpr int kFineMin = 8;                 // subtiles with at most this many keep their order
 constexpr int kFineBig = 1024;              // larger subtiles are ordered by a whole block
-constexpr int kFineWaves = 4;               // tiles (one per wave) per fine-order block
+constexpr int kFineWaves = kFineBins / kWave;   // tiles (one per wave) per fine-order block
 constexpr int kFinishWaves = 4;             // waves per block of the cluster box kernel
 constexpr int kFinishLanes = 8;             // lanes per cluster in the box kernel
 constexpr int kListCap = 224;               // screened supplier records per wave (LDS)
@@ -70,7 +70,7 @@ struct Geom {
 struct Cluster {
     int tile;     // tile index (tx*nt + ty)*nt + tz
     int subset;   // receiver subset (batched calls)
-    int begin;    // first entry in act_pos / rp / rperm
+    int begin;    // first entry in rp / rperm
     int count;    // 1..csize receivers
     double lo[3]; // bounding box of the receivers (wrapped positions)
     double hi[3];
@@ -111,71 +111,73 @@ enum SelKind { SEL_ALL = 0, SEL_MASK = 1, SEL_RUNG = 2 };
 
 // ---- work items ---------------------------------------------------------------
 
-__device__ inline int neighbour_tile(int tile, int t, const Geom &g) {
-    int tx = tile / (g.nt * g.nt), ty = (tile / g.nt) % g.nt, tz = tile % g.nt;
-    int nx = tx + t / 9 - 1, ny = ty + (t / 3) % 3 - 1, nz = tz + t % 3 - 1;
-    nx += nx < 0 ? g.nt : (nx >= g.nt ? -g.nt : 0);
-    ny += ny < 0 ? g.nt : (ny >= g.nt ? -g.nt : 0);
-    nz += nz < 0 ? g.nt : (nz >= g.nt ? -g.nt : 0);
-    return (nx * g.nt + ny) * g.nt + nz;
-}
-
 // Greedy grouping of the 27 neighbour tiles into items of about `target`
 // supplier candidates (before subtile culling); a tile holding more than
-// `target` particles is split by subtile ranges.  Returns the item count and
-// writes the items when `out` is non-null.  At most 2 per stencil tile plus
-// one with one subtile per tile (a flush and the tile itself), at most
-// 1 + ns^3 per tile plus one otherwise (plan_items_bound).
+// `target` particles is split by subtile ranges.  At most 2 items per stencil
+// tile plus one with one subtile per tile (a flush and the tile itself), at
+// most 1 + ns^3 per tile plus one otherwise (plan_items_bound).
 //
-// half != 0 (pairs evaluated once, for both partners): only the upper half
-// of the stencil, t = 13 .. 26, whose periodic mirror images are the lower
-// half; in the own tile (t = 13) only the particles after the cluster count,
-// and every cluster gets at least one item, so that its own pairs are
-// evaluated.  The first item of a cluster carries kItemFirst.
-// Upper bound on the items plan_items gives one cluster.
+// HALF (pairs evaluated once, for both partners): only the upper half of the
+// stencil, t = 13 .. 26, whose periodic mirror images are the lower half; in
+// the own tile (t = 13) only the particles after the cluster count, and every
+// cluster gets at least one item, so that its own pairs are evaluated.  The
+// first item of a cluster carries kItemFirst.
+// Upper bound on the items one cluster gets.
 inline long long plan_items_bound(int ns3, int half) {
     const long long tiles = half ? 14 : 27;
     return tiles * (ns3 == 1 ? 2 : 1 + ns3) + 2;
 }
 
-__device__ inline int plan_items(int cidx, const Cluster &cl, const int *__restrict__ cs,
-                                 const Geom &g, int target, Item *out, int sole, int half) {
-    int n = 0, acc = 0;
-    const int t_begin = half ? 13 : 0;
-    int t0 = t_begin;
-    auto emit = [&](int a, int b, int s0, int s1) {
-        if (out) {
-            Item it;
-            it.cluster = cidx;
-            it.tiles = a | (b << 8);
-            it.subs = s0 | (s1 << 16);
-            it.sole = sole | (n == 0 ? kItemFirst : 0);
-            out[n] = it;
-        }
-        ++n;
-    };
-    for (int t = t_begin; t < 27; ++t) {
-        int nb = neighbour_tile(cl.tile, t, g);
-        int w = cs[(size_t)(nb + 1) * g.ns3] - cs[(size_t)nb * g.ns3];
-        if (half && t == 13) w = cs[(size_t)(nb + 1) * g.ns3] - (cl.begin + cl.count);
-        if (w > target) {
-            if (acc > 0) emit(t0, t, 0, g.ns3);
-            int parts = min((w + target - 1) / target, g.ns3);
+// Particles of each stencil tile of the cluster [begin, begin + count) of
+// `tile` that the plan counts.  All loads are issued before any is used: the
+// plan is bound by their latency.
+template <bool HALF>
+__device__ __forceinline__ void plan_weights(int tile, int end, const int *__restrict__ cs,
+                                             const Geom &g, int (&w)[27]) {
+    constexpr int T0 = HALF ? 13 : 0;
+    const int tx = tile / (g.nt * g.nt), ty = (tile / g.nt) % g.nt, tz = tile % g.nt;
+    int lo[27], hi[27];
+#pragma unroll
+    for (int t = T0; t < 27; ++t) {
+        int nx = tx + t / 9 - 1, ny = ty + (t / 3) % 3 - 1, nz = tz + t % 3 - 1;
+        nx += nx < 0 ? g.nt : (nx >= g.nt ? -g.nt : 0);
+        ny += ny < 0 ? g.nt : (ny >= g.nt ? -g.nt : 0);
+        nz += nz < 0 ? g.nt : (nz >= g.nt ? -g.nt : 0);
+        const size_t c = (size_t)((nx * g.nt + ny) * g.nt + nz) * g.ns3;
+        lo[t] = cs[c];
+        hi[t] = cs[c + g.ns3];
+    }
+    if constexpr (HALF) lo[13] = end;
+#pragma unroll
+    for (int t = T0; t < 27; ++t) w[t] = hi[t] - lo[t];
+}
+
+// The items of one cluster in order, each handed to emit(k, t0, t1, s0, s1);
+// returns their number.
+template <bool HALF, class Emit>
+__device__ __forceinline__ int plan_items(const int (&w)[27], int target, int ns3, Emit emit) {
+    constexpr int T0 = HALF ? 13 : 0;
+    int n = 0, acc = 0, t0 = T0;
+#pragma unroll
+    for (int t = T0; t < 27; ++t) {
+        if (w[t] > target) {
+            if (acc > 0) emit(n++, t0, t, 0, ns3);
+            const int parts = min((w[t] + target - 1) / target, ns3);
             for (int q = 0; q < parts; ++q)
-                emit(t, t + 1, q * g.ns3 / parts, (q + 1) * g.ns3 / parts);
+                emit(n++, t, t + 1, q * ns3 / parts, (q + 1) * ns3 / parts);
             t0 = t + 1;
             acc = 0;
-        } else if (acc + w > target) {
-            emit(t0, t, 0, g.ns3);
+        } else if (acc + w[t] > target) {
+            emit(n++, t0, t, 0, ns3);
             t0 = t;
-            acc = w;
+            acc = w[t];
         } else {
-            if (acc == 0 && w == 0) t0 = t + 1;   // skip leading empty tiles
-            acc += w;
+            if (acc == 0 && w[t] == 0) t0 = t + 1;   // skip leading empty tiles
+            acc += w[t];
         }
     }
-    if (acc > 0) emit(t0, 27, 0, g.ns3);
-    if (half && n == 0) emit(13, 14, 0, g.ns3);
+    if (acc > 0) emit(n++, t0, 27, 0, ns3);
+    if (HALF && n == 0) emit(n++, 13, 14, 0, ns3);
     return n;
 }
 
@@ -200,14 +202,16 @@ hipError_t launch_scan1(const int *in, int *out, size_t n, unsigned long long *s
                         unsigned long long *stall, int *bsum, hipStream_t s);
 // scatter into tile -> subtile order: particles of subtiles that the fine
 // order leaves as they are (at most max(csize, kFineMin)) go to sp2/perm2/sel2,
-// the others to sp/perm/sel_s for launch_fine_order
+// the others to sp/perm/sel_s for launch_fine_order; the subtiles above
+// kFineBig particles are listed in big_list (1 + n / kFineBig ints,
+// big_list[0] zeroed before the launch)
 // stable: ranks from launch_stable_ranks (already in fine order), so every
 // subtile goes to sp2/perm2/sel2 and no fine-order pass follows
 hipError_t launch_scatter(const double *pos, const double *mass, const uint8_t *sel, int n,
                           const Geom &g, const int *key, const int *rank,
                           const int *cell_start, int fp32, int csize, bool stable, double4 *sp,
                           int *perm, uint8_t *sel_s, double4 *sp2, int *perm2, uint8_t *sel2,
-                          hipStream_t s);
+                          int *big_list, hipStream_t s);
 // Deterministic mode: rank[i] = place of particle i in its cell when the
 // cell's particles are ordered by (fine sub-cell, index) (cell_start: the
 // scanned cell counts; key: launch_keys' cell keys).  Scratch: k64a/k64b n
@@ -227,64 +231,59 @@ hipError_t launch_item_reduce(const Cluster *clusters, const int *n_clusters_dev
                               hipStream_t s);
 // reorder the particles of every subtile by the Morton index of their fine
 // sub-cell (sp/perm/sel -> sp2/perm2/sel2; sel == nullptr: no selector;
-// fkey/frank: n ints of scratch).  launch_big_list lists the subtiles above
-// kFineBig particles in big_list (1 + n / kFineBig ints, big_list[0] zeroed
-// before it); launch_fine_order_medium orders the others, and
-// launch_fine_order_big the listed ones (after launch_big_list; the two
-// orderings touch different subtiles and may run at the same time)
-hipError_t launch_big_list(const int *cell_start, const Geom &g, int *big_list, hipStream_t s);
-hipError_t launch_fine_order_medium(const double4 *sp, const int *perm, const uint8_t *sel,
-                                    const int *cell_start, const Geom &g, int *fkey, int *frank,
-                                    double4 *sp2, int *perm2, uint8_t *sel2, int csize,
-                                    hipStream_t s);
-hipError_t launch_fine_order_big(const double4 *sp, const int *perm, const uint8_t *sel,
-                                 const int *cell_start, const Geom &g, int *fkey, int *frank,
-                                 double4 *sp2, int *perm2, uint8_t *sel2, int n,
-                                 const int *big_list, hipStream_t s);
-hipError_t launch_flags(const uint8_t *sel_s, int n, int n_sub, int kind,
-                        const uint8_t *thr_host, int *flags, hipStream_t s);
-hipError_t launch_compact(const int *scan, int n, int n_sub, int *act_pos, hipStream_t s);
-// *a, *b, *c -> host_out[0..2] (pinned host memory)
-hipError_t launch_totals(const int *a, const int *b, const int *c, int *host_out,
-                         hipStream_t s);
-// scan == nullptr (one subset, every particle a receiver): receivers are the
-// sorted particles themselves
-hipError_t launch_cluster_count(const int *cell_start, const int *scan, int n, int n_sub,
-                                const Geom &g, int csize, int *ncl, hipStream_t s);
-hipError_t launch_cluster_write(const int *cell_start, const int *scan, const int *cl_off,
-                                int n, int n_sub, const Geom &g, int csize, Cluster *clusters,
-                                hipStream_t s);
-// half != 0: items over the upper half of the neighbour stencil only, for
-// the pair kernel that evaluates each pair once for both partners
-hipError_t launch_item_count(const Cluster *clusters, const int *n_clusters_dev,
-                             int cluster_bound, const int *cell_start, const Geom &g,
-                             int target, int half, int *item_cnt, hipStream_t s);
-// every cluster's items at their offsets item_off (the scanned counts; the
-// array holds them all); the cluster count is read on the device.  host_tot
-// (nullable, pinned): receives the receiver total *tot_recv, the cluster
-// count and the item total *tot_items.
+// fkey/frank: n ints of scratch; big_list from launch_scatter)
+hipError_t launch_fine_order(const double4 *sp, const int *perm, const uint8_t *sel,
+                             const int *cell_start, const Geom &g, int *fkey, int *frank,
+                             double4 *sp2, int *perm2, uint8_t *sel2, int n, int csize,
+                             const int *big_list, hipStream_t s);
+// Receivers of every subset compacted in one launch: prefix[k n + p] (n_sub n
+// + 1 ints) = receivers before particle p of subset k, and the receivers'
+// records and original indices in rp / rperm at those places.  status:
+// receivers_status_needed(n_sub n) entries and *ctr zeroed before the launch.
+size_t receivers_status_needed(size_t rows);
+hipError_t launch_receivers(const uint8_t *sel_s, int n, int n_sub, int kind,
+                            const uint8_t *thr_host, const double4 *sp, const int *perm,
+                            int *prefix, double4 *rp, int *rperm, unsigned long long *status,
+                            int *ctr, unsigned long long *stall, hipStream_t s);
+// Clusters and work items of a call in one launch.
+struct PlanArgs {
+    const int *cell_start;
+    const int *prefix;      // of launch_receivers; nullptr: every particle a receiver
+    int n, n_sub, csize, target, half;
+    Cluster *clusters;      // tile, subset, begin and count of every cluster
+    Item *items;            // nullptr: counted only
+    int *item_off;          // nullptr, or the first item of every cluster (and the total)
+    unsigned long long *status;   // plan_status_needed() entries, zeroed
+    int *ctr;                     // zeroed
+    unsigned long long *stall;
+    int *n_clusters, *n_items;    // totals on the device
+    int *host_tot;          // pinned: receivers, clusters and items
+};
+size_t plan_status_needed(int n_sub, const Geom &g);
+hipError_t launch_plan(const PlanArgs &p, const Geom &g, hipStream_t s);
+// every cluster's items at their offsets item_off of launch_plan (for arrays
+// sized after the count is known); at most `bound` clusters
 hipError_t launch_item_write(const Cluster *clusters, const int *n_clusters_dev, int bound,
                              const int *cell_start, const Geom &g, int target, int half,
-                             const int *item_off, Item *items, const int *tot_recv,
-                             const int *tot_items, int *host_tot, hipStream_t s);
+                             const int *item_off, Item *items, hipStream_t s);
 // 32-bin histogram of particles per tile (log2 bins; bin 0: empty tiles),
 // the occupancy signature the autotuner files its results under
 hipError_t launch_tile_hist(const int *cell_start, const Geom &g, int *hist32, hipStream_t s);
-hipError_t launch_gather_weights(const double *grad_acc, const uint8_t *sel_s, const int *perm,
-                                 int n, int fp32, double4 *wa, hipStream_t s);
-// per cluster: receivers copied to rp / rperm / rwa (indexed like act_pos;
-// rp == nullptr: no copy, act_pos == nullptr as scan == nullptr above) and the
-// bounding box filled in; *n_clusters_dev clusters, at most `bound`
+// the bounding box of every cluster from its receivers rp (indexed like the
+// clusters' begin); *n_clusters_dev clusters, at most `bound`.  w != nullptr
+// (the adjoint, every particle a receiver): also wa[p] = the weight of sorted
+// particle p (0 where sel is given and 0; FP32 records for fp32 calls)
 hipError_t launch_cluster_finish(Cluster *clusters, const int *n_clusters_dev, size_t bound,
-                                 int csize, const int *act_pos, const double4 *sp,
-                                 const int *perm, const double4 *wa, double4 *rp, int *rperm,
-                                 double4 *rwa, hipStream_t s);
+                                 int csize, const double4 *rp, const double *w,
+                                 const uint8_t *sel, const int *perm, int fp32, double4 *wa,
+                                 hipStream_t s);
 // up to kFillMax int regions set to their values in one launch
 constexpr int kFillMax = 8;
 struct FillSet {
     int *p[kFillMax];
     size_t n[kFillMax];
     int v[kFillMax];
+    int first[kFillMax + 1];   // set by launch_fill_multi
     int count;
     void add(int *ptr, size_t len, int val) {
         p[count] = ptr;
@@ -293,7 +292,7 @@ struct FillSet {
         ++count;
     }
 };
-hipError_t launch_fill_multi(const FillSet &f, hipStream_t s);
+hipError_t launch_fill_multi(FillSet f, hipStream_t s);
 
 // force.hip
 enum PairMode { FWD_F32 = 0, FWD_F64 = 1, BWD_F32 = 2, BWD_F64 = 3 };
@@ -305,14 +304,13 @@ constexpr int kQueueStride = 64;
 
 struct PairArgs {
     const double4 *sp;       // suppliers in sorted order
-    const double4 *rp;       // receivers, indexed like act_pos
-    const double4 *rwa;      // backward: receivers' w * [active] (FP32 path: float4 bits)
+    const double4 *rp;       // receivers
     const int *cell_start;
     const Cluster *clusters;
     const Item *items;
-    const double4 *wa;       // backward: suppliers' w * [active], sorted (FP32: float4 bits)
+    const double4 *wa;       // backward: w * [active] of the sorted particles (FP32: float4 bits)
     int *queue;              // kXcds work counters kQueueStride ints apart, zero at launch
-    const int *rperm;        // original index of each receiver row (indexed like act_pos)
+    const int *rperm;        // original index of each receiver row (indexed like rp)
     double *out;             // n_sub x n x 3, zeroed before the launch
     long long out_stride;    // elements per subset in out (3 n)
     Counters *counters;      // kCounterCopies copies, kCounterStride apart

@@ -220,18 +220,65 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(const int *in, int *ou
     }
 }
 
-// Single-pass exclusive scan (decoupled look-back).  Each block takes the
-// next tile number from a counter, so every tile before it belongs to a
-// block that is already running; it scans its tile, publishes the tile's
-// sum at once (nothing delays that), then its first wave reads the status of
-// the 64 tiles before it together, adding their sums back to the nearest
-// published inclusive prefix (another window of 64 if there is none), and
-// publishes its own.  status[t] (zeroed before the launch): 0 nothing yet,
-// 1 << 32 | sum, or 2 << 32 | inclusive prefix.  A wait longer than
-// kScan1Spins polls (which a running predecessor cannot cause) ends the wait
-// anyway and raises *stall.  out[n] = the total; in may equal out.
-constexpr unsigned long long kScanSum = 1ull << 32, kScanPrefix = 2ull << 32;
-constexpr int kScan1Spins = 1 << 20;
+// Decoupled look-back.  Each block takes the next tile number from a counter,
+// so every tile before it belongs to a block that is already running; it
+// publishes its tile's sum at once (nothing delays that), then its first wave
+// reads the status of the 64 tiles before it together, adding their sums back
+// to the nearest published inclusive prefix (another window of 64 if there is
+// none), and publishes its own.  status[t] (zeroed before the launch): 0
+// nothing yet, kBackSum | sum, or kBackPrefix | inclusive prefix, with 62 bits
+// of value (one sum, or two that are packed).  A wait longer than kBackSpins
+// polls (which a running predecessor cannot cause) ends the wait anyway and
+// raises *stall.
+constexpr unsigned long long kBackSum = 1ull << 62, kBackPrefix = 2ull << 62;
+constexpr unsigned long long kBackValue = kBackSum - 1ull;
+constexpr int kBackSpins = 1 << 20;
+
+// The sum of the tiles before t (every lane of the calling wave, which all
+// must take part); publishes tile t's own sum `total`.
+__device__ __forceinline__ unsigned long long look_back(unsigned long long *status, int t,
+                                                        unsigned long long total,
+                                                        unsigned long long *stall) {
+    const int lane = threadIdx.x & (kWave - 1);
+    if (lane == 0)
+        __hip_atomic_store(&status[t], (t == 0 ? kBackPrefix : kBackSum) | total,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long excl = 0;
+    for (int top = t - 1; top >= 0; top -= kWave) {
+        // tiles before 0 count as a prefix of 0, so every window that
+        // reaches them ends the walk
+        const int p = top - lane;
+        int spins = 0;
+        int near = kWave;   // lowest lane (nearest tile) holding a prefix
+        unsigned long long st = 0;
+        for (;;) {
+            st = p >= 0 ? __hip_atomic_load(&status[p], __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT)
+                        : kBackPrefix;
+            const unsigned long long pm = __builtin_amdgcn_ballot_w64((st >> 62) == 2);
+            const unsigned long long em = __builtin_amdgcn_ballot_w64((st >> 62) == 0);
+            near = pm ? __builtin_ctzll(pm) : kWave;
+            const unsigned long long need = near >= kWave - 1 ? ~0ull : ((2ull << near) - 1ull);
+            if ((em & need) == 0) break;
+            if (++spins >= kBackSpins) {
+                if (lane == 0) atomicAdd(stall, 1ull);
+                near = -1;   // give up: the result is flagged as invalid
+                break;
+            }
+        }
+        if (near < 0) break;
+        unsigned long long add = lane <= near ? st & kBackValue : 0ull;
+        for (int off = kWave / 2; off > 0; off >>= 1) add += __shfl_xor(add, off, kWave);
+        excl += add;
+        if (near < kWave) break;
+    }
+    if (lane == 0 && t > 0)
+        __hip_atomic_store(&status[t], kBackPrefix | (excl + total), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    return excl;
+}
+
+// Single-pass exclusive scan.  out[n] = the total; in may equal out.
 constexpr int kScan1MaxTiles = 64;   // larger scans take the three-kernel path
 
 __global__ __launch_bounds__(kScanBlock) void k_scan_1pass(const int *in, int *out, size_t n,
@@ -262,45 +309,8 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_1pass(const int *in, int *o
     int total;
     int run = block_exclusive_scan(sum, lds, &total);
     if (threadIdx.x < kWave) {
-        // the first wave: publish the tile's sum, then look back over the
-        // 64 tiles before the window's top at once; tiles before 0 count as
-        // a prefix of 0, so every window that reaches them ends the walk
-        const int lane = threadIdx.x;
-        if (lane == 0)
-            __hip_atomic_store(&status[t], (t == 0 ? kScanPrefix : kScanSum) | (unsigned)total,
-                               __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        int excl = 0;
-        for (int top = t - 1; top >= 0; top -= kWave) {
-            const int p = top - lane;
-            int spins = 0;
-            int near = kWave;   // lowest lane (nearest tile) holding a prefix
-            unsigned long long st = 0;
-            for (;;) {
-                st = p >= 0 ? __hip_atomic_load(&status[p], __ATOMIC_ACQUIRE,
-                                                 __HIP_MEMORY_SCOPE_AGENT)
-                            : kScanPrefix;
-                const unsigned long long pm = __builtin_amdgcn_ballot_w64((st >> 32) == 2);
-                const unsigned long long em = __builtin_amdgcn_ballot_w64((st >> 32) == 0);
-                near = pm ? __builtin_ctzll(pm) : kWave;
-                const unsigned long long need =
-                    near >= kWave - 1 ? ~0ull : ((2ull << near) - 1ull);
-                if ((em & need) == 0) break;
-                if (++spins >= kScan1Spins) {
-                    if (lane == 0) atomicAdd(stall, 1ull);
-                    near = -1;   // give up: the result is flagged as invalid
-                    break;
-                }
-            }
-            if (near < 0) break;
-            int add = lane <= near ? (int)(unsigned)(st & 0xffffffffull) : 0;
-            for (int off = kWave / 2; off > 0; off >>= 1) add += __shfl_xor(add, off, kWave);
-            excl += add;
-            if (near < kWave) break;
-        }
-        if (lane == 0) {
-            if (t > 0)
-                __hip_atomic_store(&status[t], kScanPrefix | (unsigned)(excl + total),
-                                   __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        const int excl = (int)look_back(status, t, (unsigned)total, stall);
+        if (threadIdx.x == 0) {
             s_excl = excl;
             if (base + kScanTile >= n) out[n] = excl + total;   // the last tile
         }
@@ -332,13 +342,17 @@ __global__ void k_scatter(const double *__restrict__ pos, const double *__restri
                           const int *__restrict__ cell_start, int fp32, int keep_max,
                           double4 *__restrict__ sp_s, int *__restrict__ perm_s,
                           uint8_t *__restrict__ sel_st, double4 *__restrict__ sp_f,
-                          int *__restrict__ perm_f, uint8_t *__restrict__ sel_f) {
+                          int *__restrict__ perm_f, uint8_t *__restrict__ sel_f,
+                          int *__restrict__ big_list) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int k = key[i];
-    const int c0 = cell_start[k];
-    int dst = c0 + rank[i];
-    const bool direct = cell_start[k + 1] - c0 <= keep_max;
+    const int c0 = cell_start[k], cnt = cell_start[k + 1] - c0;
+    const int q = rank[i];
+    int dst = c0 + q;
+    const bool direct = cnt <= keep_max;
+    // the particle of rank 0 lists its subtile for the block-wide fine order
+    if (q == 0 && !direct && cnt > kFineBig) big_list[1 + atomicAdd(big_list, 1)] = k;
     double4 *__restrict__ sp = direct ? sp_f : sp_s;
     int *__restrict__ perm = direct ? perm_f : perm_s;
     uint8_t *__restrict__ sel_s = direct ? sel_f : sel_st;
@@ -385,31 +399,67 @@ __device__ inline void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Fine order, medium subtiles: one wave per tile, kFineWaves tiles per
-// block.  Inside every subtile holding more than keep_max and at most
-// kFineBig particles the particles are reordered by fine_key (a counting sort
-// over kFineBins bins in LDS); smaller subtiles are already in place (the
-// scatter wrote them to sp2/perm2/sel2); larger ones are k_fine_order_big's,
-// which can run at the same time.  Reads sp/perm/sel and writes sp2/perm2/sel2
-// (sel == nullptr: no selector); fkey/frank are scratch indexed by sorted
-// position.  Consecutive receivers then lie close together, so small
-// clusters have small bounding boxes.
-__global__ __launch_bounds__(kFineWaves * kWave) void k_fine_order(
+// Fine order.  Inside every subtile holding more than keep_max particles the
+// particles are reordered by fine_key (a counting sort over kFineBins bins in
+// LDS); smaller subtiles are already in place (the scatter wrote them to
+// sp2/perm2/sel2).  Reads sp/perm/sel and writes sp2/perm2/sel2 (sel ==
+// nullptr: no selector); fkey/frank are scratch indexed by sorted position.
+// Consecutive receivers then lie close together, so small clusters have small
+// bounding boxes.
+//
+// The first big_blocks blocks take the subtiles above kFineBig particles
+// (listed by the scatter: big_list[0] counts them, the ids follow in any
+// order), one after the other with one bin per thread in the scan: a single
+// wave would take the densest halo cores alone, long after the rest of the
+// grid.  The other blocks take one tile per wave.  Both in one launch, so
+// that the dense subtiles run beside the rest without a second stream (whose
+// events cost the call 6 to 12 us each).
+__global__ __launch_bounds__(kFineBins) void k_fine_order(
     const double4 *__restrict__ sp, const int *__restrict__ perm, const uint8_t *__restrict__ sel,
     const int *__restrict__ cs, Geom g, int *__restrict__ fkey, int *__restrict__ frank,
     double4 *__restrict__ sp2, int *__restrict__ perm2, uint8_t *__restrict__ sel2, int keep_max,
-    int *__restrict__) {
+    int big_blocks, const int *__restrict__ big_list) {
     __shared__ int hists[kFineWaves][kFineBins];
+    if ((int)blockIdx.x < big_blocks) {
+        int *hist = hists[0];
+        int *lds = hists[1];
+        const int t = threadIdx.x;
+        const int n_big = big_list[0];
+        for (int j = blockIdx.x; j < n_big; j += big_blocks) {
+            const int cell = big_list[1 + j];
+            const int a0 = cs[cell], a1 = cs[cell + 1];
+            hist[t] = 0;
+            __syncthreads();
+            for (int i = a0 + t; i < a1; i += kFineBins) {
+                const int k = fine_key(sp[i], g);
+                fkey[i] = k;
+                frank[i] = atomicAdd(&hist[k], 1);
+            }
+            __syncthreads();
+            int total;
+            const int ex = block_exclusive_scan(hist[t], lds, &total);
+            hist[t] = ex;   // every thread has read its own bin in the call above
+            __syncthreads();
+            for (int i = a0 + t; i < a1; i += kFineBins) {
+                const int dst = a0 + hist[fkey[i]] + frank[i];
+                sp2[dst] = sp[i];
+                perm2[dst] = perm[i];
+                if (sel) sel2[dst] = sel[i];
+            }
+            __syncthreads();
+        }
+        return;
+    }
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x / kWave;
     int *hist = hists[w];
-    for (long long tile = (long long)blockIdx.x * kFineWaves + w; tile < g.nt3;
-         tile += (long long)gridDim.x * kFineWaves) {
+    const long long stride = (long long)(gridDim.x - big_blocks) * kFineWaves;
+    for (long long tile = (long long)(blockIdx.x - big_blocks) * kFineWaves + w; tile < g.nt3;
+         tile += stride) {
         const int *c = cs + tile * g.ns3;
         for (int s = 0; s < g.ns3; ++s) {
             const int a0 = c[s], a1 = c[s + 1];
-            if (a1 - a0 <= keep_max) continue;   // written in place by k_scatter
-            if (a1 - a0 > kFineBig) continue;   // listed by k_big_list
+            if (a1 - a0 <= keep_max || a1 - a0 > kFineBig) continue;
             for (int b = lane; b < kFineBins; b += kWave) hist[b] = 0;
             wave_lds_sync();
             for (int i = a0 + lane; i < a1; i += kWave) {
@@ -446,52 +496,6 @@ __global__ __launch_bounds__(kFineWaves * kWave) void k_fine_order(
             }
             wave_lds_sync();
         }
-    }
-}
-
-// The subtiles holding more than kFineBig particles (big_list[0] counts
-// them, zeroed before the launch; the ids follow in any order).
-__global__ void k_big_list(const int *__restrict__ cs, long long cells, int *__restrict__ big_list) {
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells) return;
-    if (cs[c + 1] - cs[c] > kFineBig) big_list[1 + atomicAdd(big_list, 1)] = (int)c;
-}
-
-// Fine order of the subtiles holding more than kFineBig particles (listed
-// by k_big_list): one block of kFineBins threads per subtile, the same
-// counting sort with one bin per thread in the scan.  A single wave would
-// take the densest halo cores alone, long after the rest of the grid.
-__global__ __launch_bounds__(kFineBins) void k_fine_order_big(
-    const double4 *__restrict__ sp, const int *__restrict__ perm, const uint8_t *__restrict__ sel,
-    const int *__restrict__ cs, Geom g, int *__restrict__ fkey, int *__restrict__ frank,
-    double4 *__restrict__ sp2, int *__restrict__ perm2, uint8_t *__restrict__ sel2,
-    const int *__restrict__ big_list) {
-    __shared__ int hist[kFineBins];
-    __shared__ int lds[kFineBins / kWave];
-    const int t = threadIdx.x;
-    const int n_big = big_list[0];
-    for (int j = blockIdx.x; j < n_big; j += gridDim.x) {
-        const int cell = big_list[1 + j];
-        const int a0 = cs[cell], a1 = cs[cell + 1];
-        hist[t] = 0;
-        __syncthreads();
-        for (int i = a0 + t; i < a1; i += kFineBins) {
-            const int k = fine_key(sp[i], g);
-            fkey[i] = k;
-            frank[i] = atomicAdd(&hist[k], 1);
-        }
-        __syncthreads();
-        int total;
-        const int ex = block_exclusive_scan(hist[t], lds, &total);
-        hist[t] = ex;   // every thread has read its own bin in the call above
-        __syncthreads();
-        for (int i = a0 + t; i < a1; i += kFineBins) {
-            const int dst = a0 + hist[fkey[i]] + frank[i];
-            sp2[dst] = sp[i];
-            perm2[dst] = perm[i];
-            if (sel) sel2[dst] = sel[i];
-        }
-        __syncthreads();
     }
 }
 
@@ -592,96 +596,228 @@ __global__ void k_rs_rank(const unsigned long long *__restrict__ k64,
 
 struct Thresholds { uint8_t t[64]; };
 
-__global__ void k_flags(const uint8_t *__restrict__ sel_s, int n, int n_sub, int kind,
-                        Thresholds thr, int *__restrict__ flags) {
-    size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t total = (size_t)n * n_sub;
-    if (idx >= total) return;
-    int k = (int)(idx / n);
-    int p = (int)(idx - (size_t)k * n);
-    int f;
-    if (kind == SEL_ALL) f = 1;
-    else if (kind == SEL_MASK) f = sel_s[p] != 0;
-    else f = sel_s[p] >= thr.t[k];
-    flags[idx] = f;
-}
+// Compaction of the receivers, subset-major in sorted order, in one pass over
+// the (subset, particle) rows: tiles of kRecvTile rows, 256 ballots of
+// 64 consecutive rows each; the ballots' counts are scanned over the block and
+// a look-back gives the receivers of the tiles before.  prefix[row] = the
+// receivers before the row (prefix[rows] the total); the receivers' records
+// and original indices are gathered at their places.  (Flags, a scan of three
+// kernels over them, the compaction and the gather were six launches.)
+constexpr int kRecvThreads = 1024;
+constexpr int kRecvPer = 16;   // rows per thread
+constexpr int kRecvTile = kRecvThreads * kRecvPer;
+constexpr int kRecvWaves = kRecvThreads / kWave;
 
-__global__ void k_compact(const int *__restrict__ scan, int n, int n_sub, int *__restrict__ act_pos) {
-    size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t total = (size_t)n * n_sub;
-    if (idx >= total) return;
-    int a = scan[idx];
-    if (scan[idx + 1] > a) {
-        int k = (int)(idx / n);
-        act_pos[a] = (int)(idx - (size_t)k * n);
+__global__ __launch_bounds__(kRecvThreads) void k_receivers(
+    const uint8_t *__restrict__ sel_s, int n, int n_sub, int kind, Thresholds thr,
+    const double4 *__restrict__ sp, const int *__restrict__ perm, int *__restrict__ prefix,
+    double4 *__restrict__ rp, int *__restrict__ rperm, unsigned long long *status, int *ctr,
+    unsigned long long *stall) {
+    __shared__ int cnt[kRecvPer * kRecvWaves];
+    __shared__ int lds[kRecvWaves];
+    __shared__ int s_tile, s_excl;
+    if (threadIdx.x == 0) s_tile = atomicAdd(ctr, 1);
+    __syncthreads();
+    const int tile = s_tile;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const size_t rows = (size_t)n * n_sub;
+    const size_t first = (size_t)tile * kRecvTile + threadIdx.x;
+    const int k0 = (int)(first / n), p0 = (int)(first - (size_t)k0 * n);
+    unsigned flag = 0;
+    int k = k0, p = p0;
+#pragma unroll
+    for (int j = 0; j < kRecvPer; ++j) {
+        bool f = false;
+        if (first + (size_t)j * kRecvThreads < rows)
+            f = kind == SEL_MASK ? sel_s[p] != 0 : sel_s[p] >= thr.t[k];
+        flag |= (unsigned)f << j;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(f);
+        if (lane == 0) cnt[j * kRecvWaves + wave] = __builtin_popcountll(m);
+        for (p += kRecvThreads; p >= n; p -= n) ++k;
+    }
+    __syncthreads();
+    const int v = threadIdx.x < kRecvPer * kRecvWaves ? cnt[threadIdx.x] : 0;
+    int total;
+    const int ex = block_exclusive_scan(v, lds, &total);
+    if (wave == 0) {
+        const int excl = (int)look_back(status, tile, (unsigned)total, stall);
+        if (lane == 0) {
+            s_excl = excl;
+            if ((size_t)(tile + 1) * kRecvTile >= rows) prefix[rows] = excl + total;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kRecvPer * kRecvWaves) cnt[threadIdx.x] = s_excl + ex;
+    __syncthreads();
+    k = k0;
+    p = p0;
+#pragma unroll
+    for (int j = 0; j < kRecvPer; ++j) {
+        const bool f = (flag >> j) & 1u;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(f);
+        const size_t row = first + (size_t)j * kRecvThreads;
+        if (row < rows) {
+            const int at = cnt[j * kRecvWaves + wave] +
+                           __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            prefix[row] = at;
+            if (f) {
+                rp[at] = sp[p];
+                rperm[at] = perm[p];
+            }
+        }
+        for (p += kRecvThreads; p >= n; p -= n) ++k;
     }
 }
 
-__global__ void k_cluster_count(const int *__restrict__ cs, const int *__restrict__ scan, int n,
-                                int n_sub, Geom g, int csize, int *__restrict__ ncl) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_sub * g.nt3) return;
-    int k = idx / g.nt3;
-    int t = idx - k * g.nt3;
-    size_t off = (size_t)k * n;
-    // scan == nullptr: every particle is a receiver (one subset)
-    const int b0 = cs[(size_t)t * g.ns3], b1 = cs[(size_t)(t + 1) * g.ns3];
-    int a0 = scan ? scan[off + b0] : b0;
-    int a1 = scan ? scan[off + b1] : b1;
-    ncl[idx] = (a1 - a0 + csize - 1) / csize;
-}
+// ---- clusters and work items -----------------------------------------------------
 
-__global__ void k_cluster_write(const int *__restrict__ cs, const int *__restrict__ scan, int n,
-                                int n_sub, Geom g, int csize, const int *__restrict__ cl_off,
-                                Cluster *__restrict__ clusters) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_sub * g.nt3) return;
-    int k = idx / g.nt3;
-    int t = idx - k * g.nt3;
-    size_t off = (size_t)k * n;
-    const int b0 = cs[(size_t)t * g.ns3], b1 = cs[(size_t)(t + 1) * g.ns3];
-    int a0 = scan ? scan[off + b0] : b0;
-    int a1 = scan ? scan[off + b1] : b1;
-    int o = cl_off[idx];
-    for (int b = a0; b < a1; b += csize) {
-        Cluster c{};
-        c.tile = t;
-        c.subset = k;
-        c.begin = b;
-        c.count = min(csize, a1 - b);
-        clusters[o++] = c;
+// Clusters and items of PT (subset, tile) entries per block, in one
+// launch: a cluster is a run of at most csize consecutive receivers of one
+// tile, so the clusters follow from the tiles' receiver counts, and a
+// cluster's items from those and the particle counts of its stencil.  The
+// block counts its clusters (one thread per entry) and their items (one thread
+// per cluster, 256 at a time), a look-back over the blocks gives the clusters
+// and items before its own (both counts packed in one status word), and the
+// records are written where they belong: in entry order, as the XCD chunks of
+// the item queue want them.  Counting, scanning and writing clusters and items
+// in launches of their own took six, at 5 to 12 us each for sets of any size
+// below 2^20 particles.
+//
+// The look-back chain grows with the blocks (64 predecessors per step), the
+// serial work of a block with its entries: PT = 64 entries up to 2^14 of them
+// (256 blocks), 512 entries beyond.
+constexpr int kPlanThreads = 256;
+constexpr int kPlanThreadsBig = 512;
+constexpr long long kPlanBigFrom = 1 << 14;
+constexpr int kPlanCache = 1024;   // item counts kept from the first pass
+constexpr unsigned kPlanBits = 31;
+
+template <bool HALF, int PT, int NT>
+__global__ __launch_bounds__(NT) void k_plan(PlanArgs a, Geom g) {
+    __shared__ int lds[NT / kWave];
+    __shared__ int pre[PT], beg[PT], num[PT];
+    __shared__ unsigned short cache[kPlanCache];
+    __shared__ int s_tile, s_cl, s_it;
+    const int t = threadIdx.x;
+    if (t == 0) s_tile = atomicAdd(a.ctr, 1);
+    __syncthreads();
+    const int blk = s_tile;
+    const long long entries = (long long)a.n_sub * g.nt3;
+    const long long e0 = (long long)blk * PT;
+    int ncl = 0;
+    if (t < PT && e0 + t < entries) {
+        const int k = (int)((e0 + t) / g.nt3);
+        const int tile = (int)(e0 + t - (long long)k * g.nt3);
+        int r0 = a.cell_start[(size_t)tile * g.ns3], r1 = a.cell_start[(size_t)(tile + 1) * g.ns3];
+        if (a.prefix) {
+            const size_t off = (size_t)k * a.n;
+            r0 = a.prefix[off + r0];
+            r1 = a.prefix[off + r1];
+        }
+        beg[t] = r0;
+        num[t] = r1 - r0;
+        ncl = (r1 - r0 + a.csize - 1) / a.csize;
+    }
+    int n_cl;
+    const int ex = block_exclusive_scan(ncl, lds, &n_cl);
+    if (t < PT) pre[t] = ex;
+    __syncthreads();
+    // cluster c of the block: its entry is the last with pre <= c
+    auto locate = [&](int c, Cluster &cl) {
+        int lo = 0, hi = PT;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= c) lo = mid;
+            else hi = mid;
+        }
+        const int skip = (c - pre[lo]) * a.csize;
+        cl.subset = (int)((e0 + lo) / g.nt3);
+        cl.tile = (int)(e0 + lo - (long long)cl.subset * g.nt3);
+        cl.begin = beg[lo] + skip;
+        cl.count = min(a.csize, num[lo] - skip);
+    };
+    auto nothing = [](int, int, int, int, int) {};
+    int mine = 0;
+    for (int c = t; c < n_cl; c += NT) {
+        Cluster cl;
+        locate(c, cl);
+        int w[27];
+        plan_weights<HALF>(cl.tile, cl.begin + cl.count, a.cell_start, g, w);
+        const int k = plan_items<HALF>(w, a.target, g.ns3, nothing);
+        if (c < kPlanCache) cache[c] = (unsigned short)min(k, 0xffff);
+        mine += k;
+    }
+    int n_it;
+    (void)block_exclusive_scan(mine, lds, &n_it);
+    if (t < kWave) {
+        const unsigned long long excl = look_back(
+            a.status, blk, (unsigned long long)n_cl << kPlanBits | (unsigned)n_it, a.stall);
+        if (t == 0) {
+            s_cl = (int)(excl >> kPlanBits);
+            s_it = (int)(excl & ((1u << kPlanBits) - 1u));
+            if (e0 + PT >= entries) {   // the last block
+                const int all_cl = s_cl + n_cl, all_it = s_it + n_it;
+                *a.n_clusters = all_cl;
+                *a.n_items = all_it;
+                if (a.item_off) a.item_off[all_cl] = all_it;
+                a.host_tot[0] = a.prefix ? a.prefix[(size_t)a.n * a.n_sub] : a.n;
+                a.host_tot[1] = all_cl;
+                a.host_tot[2] = all_it;
+            }
+        }
+    }
+    __syncthreads();
+    const int cl0 = s_cl;
+    int it0 = s_it;
+    for (int c0 = 0; c0 < n_cl; c0 += NT) {
+        const int c = c0 + t;
+        Cluster cl{};
+        int w[27];
+        int k = 0;
+        if (c < n_cl) {
+            locate(c, cl);
+            *reinterpret_cast<int4 *>(a.clusters + cl0 + c) =
+                make_int4(cl.tile, cl.subset, cl.begin, cl.count);
+            plan_weights<HALF>(cl.tile, cl.begin + cl.count, a.cell_start, g, w);
+            k = c < kPlanCache ? cache[c] : 0xffff;
+            if (k == 0xffff) k = plan_items<HALF>(w, a.target, g.ns3, nothing);
+        }
+        int total;
+        const int off = it0 + block_exclusive_scan(k, lds, &total);
+        if (c < n_cl) {
+            if (a.item_off) a.item_off[cl0 + c] = off;
+            if (a.items) {
+                const int sole = k == 1 ? kItemSole : 0;
+                Item *out = a.items + off;
+                plan_items<HALF>(w, a.target, g.ns3, [&](int q, int t0, int t1, int s0, int s1) {
+                    *reinterpret_cast<int4 *>(out + q) =
+                        make_int4(cl0 + c, t0 | (t1 << 8), s0 | (s1 << 16),
+                                  sole | (q == 0 ? kItemFirst : 0));
+                });
+            }
+        }
+        it0 += total;
     }
 }
 
-// ---- work items ------------------------------------------------------------
-
-__global__ void k_item_count(const Cluster *__restrict__ clusters, const int *__restrict__ n_cl,
-                             int bound, const int *__restrict__ cs, Geom g, int target, int half,
-                             int *__restrict__ item_cnt) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= bound) return;
-    item_cnt[c] = c < *n_cl ? plan_items(c, clusters[c], cs, g, target, nullptr, 0, half) : 0;
-}
-
-// Items of every cluster at their scanned offsets; the cluster count is
-// read on the device.
-// tot (nullable): the call's receiver, cluster and item totals (three device
-// counters) copied to the pinned host array host_tot by the first thread,
-// so no launch after the pair kernel is needed for them.
+// Items of every cluster at their offsets; the cluster count is read on the
+// device.
+template <bool HALF>
 __global__ void k_item_write(const Cluster *__restrict__ clusters, const int *__restrict__ n_cl,
-                             int bound, const int *__restrict__ cs, Geom g, int target, int half,
-                             const int *__restrict__ item_off, Item *__restrict__ items,
-                             const int *tot_recv, const int *tot_items, int *host_tot) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (host_tot && c == 0) {
-        host_tot[0] = *tot_recv;
-        host_tot[1] = *n_cl;
-        host_tot[2] = *tot_items;
-    }
-    if (c >= bound || c >= *n_cl) return;
+                             const int *__restrict__ cs, Geom g, int target,
+                             const int *__restrict__ item_off, Item *__restrict__ items) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= *n_cl) return;
     const int off = item_off[c];
-    plan_items(c, clusters[c], cs, g, target, items + off,
-               item_off[c + 1] - off == 1 ? kItemSole : 0, half);
+    const int sole = item_off[c + 1] - off == 1 ? kItemSole : 0;
+    const Cluster &cl = clusters[c];
+    int w[27];
+    plan_weights<HALF>(cl.tile, cl.begin + cl.count, cs, g, w);
+    plan_items<HALF>(w, target, g.ns3, [&](int q, int t0, int t1, int s0, int s1) {
+        *reinterpret_cast<int4 *>(items + off + q) = make_int4(
+            c, t0 | (t1 << 8), s0 | (s1 << 16), sole | (q == 0 ? kItemFirst : 0));
+    });
 }
 
 // Deterministic mode: the sums of every cluster with several items, added
@@ -712,51 +848,20 @@ __global__ __launch_bounds__(kWave) void k_item_reduce(
     }
 }
 
-__global__ void k_gather_weights(const double *__restrict__ w, const uint8_t *__restrict__ sel_s,
-                                 const int *__restrict__ perm, int n, int fp32,
-                                 double4 *__restrict__ wa) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    size_t i = (size_t)perm[p];
-    double x = 0, y = 0, z = 0;
-    if (!sel_s || sel_s[p]) {   // no selector: all active
-        x = w[3 * i];
-        y = w[3 * i + 1];
-        z = w[3 * i + 2];
-    }
-    if (fp32) {
-        reinterpret_cast<float4 *>(wa)[p] = make_float4((float)x, (float)y, (float)z, 0.0f);
-    } else {
-        wa[p] = make_double4(x, y, z, 0.0);
-    }
-}
-
-__device__ inline double wave_min(double v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-__device__ inline double wave_max(double v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
-// Receivers of each cluster gathered into contiguous arrays (rp / rperm /
-// rwa, skipped when rp == nullptr: the receivers are then the sorted
-// particles themselves, act_pos == nullptr) and the cluster's bounding box.
-// A group of kFinishLanes lanes per cluster, kWave / kFinishLanes clusters
-// per wave, kFinishWaves waves per block; each lane takes PPL = csize /
-// kFinishLanes receivers, loaded together (the kernel is bound by the
-// latency of the two dependent loads, the record and then the receivers, so
-// fewer and fuller waves finish sooner), and entries past a cluster's count
-// repeat its first receiver.  The cluster count is read on the device, so
-// the launch can be sized by an upper bound before the count reaches the
-// host.
+// The bounding box of each cluster, and for the adjoint (w != nullptr, every
+// particle a receiver) the weights of its particles in sorted order.  A group
+// of kFinishLanes lanes per cluster, kWave / kFinishLanes clusters per wave,
+// kFinishWaves waves per block; each lane takes PPL = csize / kFinishLanes
+// receivers, loaded together (the kernel is bound by the latency of the two
+// dependent loads, the record and then the receivers, so fewer and fuller
+// waves finish sooner), and entries past a cluster's count repeat its first
+// receiver.  The cluster count is read on the device, so the launch can be
+// sized by an upper bound before the count reaches the host.
 template <int PPL>
 __global__ __launch_bounds__(kFinishWaves * kWave) void k_cluster_finish(
     Cluster *__restrict__ clusters, const int *__restrict__ n_clusters_dev,
-    const int *__restrict__ act_pos, const double4 *__restrict__ sp, const int *__restrict__ perm,
-    const double4 *__restrict__ wa, double4 *__restrict__ rp, int *__restrict__ rperm,
-    double4 *__restrict__ rwa) {
+    const double4 *__restrict__ rp, const double *__restrict__ w, const uint8_t *__restrict__ sel,
+    const int *__restrict__ perm, int fp32, double4 *__restrict__ wa) {
     constexpr int per_wave = kWave / kFinishLanes;
     const int n_clusters = *n_clusters_dev;
     const int lane = threadIdx.x & (kWave - 1);
@@ -772,13 +877,26 @@ __global__ __launch_bounds__(kFinishWaves * kWave) void k_cluster_finish(
 #pragma unroll
         for (int k = 0; k < PPL; ++k) {
             const int q = li + kFinishLanes * k;
-            const int a = begin + (q < count ? q : 0);
-            const int p = act_pos ? act_pos[a] : a;
-            x[k] = sp[p];
-            if (q < count && rp) {
-                rp[a] = x[k];
-                rperm[a] = perm[p];
-                if (rwa) rwa[a] = wa[p];
+            x[k] = rp[begin + (q < count ? q : 0)];
+        }
+        if (w) {
+#pragma unroll
+            for (int k = 0; k < PPL; ++k) {
+                const int q = li + kFinishLanes * k;
+                if (q >= count) continue;
+                const int p = begin + q;
+                double wx = 0.0, wy = 0.0, wz = 0.0;
+                if (!sel || sel[p]) {   // no selector: all active
+                    const double *src = w + 3 * (size_t)perm[p];
+                    wx = src[0];
+                    wy = src[1];
+                    wz = src[2];
+                }
+                if (fp32)
+                    reinterpret_cast<float4 *>(wa)[p] =
+                        make_float4((float)wx, (float)wy, (float)wz, 0.0f);
+                else
+                    wa[p] = make_double4(wx, wy, wz, 0.0);
             }
         }
         lx = hx = x[0].x;
@@ -805,21 +923,30 @@ __global__ __launch_bounds__(kFinishWaves * kWave) void k_cluster_finish(
         hz = fmax(hz, __shfl_xor(hz, off, kWave));
     }
     if (have && li == 0) {
-        // only the box: the item kernels may read the other fields meanwhile
         Cluster *o = clusters + c;
         o->lo[0] = lx; o->lo[1] = ly; o->lo[2] = lz;
         o->hi[0] = hx; o->hi[1] = hy; o->hi[2] = hz;
     }
 }
 
-// Several int fills in one launch: region blockIdx.y, grid-stride over it.
+// Several int fills in one launch, 16 bytes per store between the unaligned
+// ends: region r takes the blocks from first[r] on.
 __global__ void k_fill_multi(FillSet f) {
-    const int r = blockIdx.y;
+    int r = 0;
+    while (r + 1 < f.count && (int)blockIdx.x >= f.first[r + 1]) ++r;
     int *__restrict__ p = f.p[r];
     const size_t n = f.n[r];
     const int v = f.v[r];
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
+    const size_t i = (size_t)(blockIdx.x - f.first[r]) * blockDim.x + threadIdx.x;
+    const size_t stride = (size_t)(f.first[r + 1] - f.first[r]) * blockDim.x;
+    const size_t mis = ((16 - ((uintptr_t)p & 15)) & 15) / sizeof(int);
+    const size_t head = mis < n ? mis : n;
+    const size_t n4 = (n - head) / 4;
+    if (i < head) p[i] = v;
+    int4 *p4 = reinterpret_cast<int4 *>(p + head);
+    const int4 v4 = make_int4(v, v, v, v);
+    for (size_t j = i; j < n4; j += stride) p4[j] = v4;
+    if (head + 4 * n4 + i < n) p[head + 4 * n4 + i] = v;   // at most 3 ints: the first threads
 }
 
 inline unsigned grid_for(size_t n, int block) {
@@ -830,9 +957,9 @@ inline unsigned grid_for(size_t n, int block) {
 }  // namespace
 
 hipError_t launch_cluster_finish(Cluster *clusters, const int *n_clusters_dev, size_t bound,
-                                 int csize, const int *act_pos, const double4 *sp,
-                                 const int *perm, const double4 *wa, double4 *rp, int *rperm,
-                                 double4 *rwa, hipStream_t s) {
+                                 int csize, const double4 *rp, const double *w,
+                                 const uint8_t *sel, const int *perm, int fp32, double4 *wa,
+                                 hipStream_t s) {
     if (bound == 0) return hipSuccess;
     const size_t per_block = (size_t)kFinishWaves * (kWave / kFinishLanes);
     if (csize != 8 && csize != 16 && csize != 32 && csize != 64) return hipErrorInvalidValue;
@@ -841,17 +968,17 @@ hipError_t launch_cluster_finish(Cluster *clusters, const int *n_clusters_dev, s
               : csize == 32 ? k_cluster_finish<4>
                             : k_cluster_finish<8>;
     hipLaunchKernelGGL(fn, dim3(grid_for(bound, (int)per_block)), dim3(kFinishWaves * kWave), 0,
-                       s, clusters, n_clusters_dev, act_pos, sp, perm, wa, rp, rperm, rwa);
+                       s, clusters, n_clusters_dev, rp, w, sel, perm, fp32, wa);
     return hipGetLastError();
 }
 
-hipError_t launch_fill_multi(const FillSet &f, hipStream_t s) {
-    size_t most = 0;
-    for (int r = 0; r < f.count; ++r) most = std::max(most, f.n[r]);
-    if (most == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_multi,
-                       dim3((unsigned)std::min<size_t>(grid_for(most, 256), 4096), f.count),
-                       dim3(256), 0, s, f);
+hipError_t launch_fill_multi(FillSet f, hipStream_t s) {
+    // 16 KB per block, at most 2048 blocks per region
+    for (int r = 0; r < f.count; ++r)
+        f.first[r + 1] =
+            f.first[r] + (f.n[r] ? (int)std::min<size_t>(grid_for(f.n[r], 4096), 2048) : 0);
+    if (f.first[f.count] == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fill_multi, dim3((unsigned)f.first[f.count]), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 
@@ -928,115 +1055,70 @@ hipError_t launch_scatter(const double *pos, const double *mass, const uint8_t *
                           const Geom &g, const int *key, const int *rank, const int *cell_start,
                           int fp32, int csize, bool stable, double4 *sp, int *perm,
                           uint8_t *sel_s, double4 *sp2, int *perm2, uint8_t *sel2,
-                          hipStream_t s) {
+                          int *big_list, hipStream_t s) {
     if (n == 0) return hipSuccess;
     // stable ranks are already in fine order: every subtile goes straight out
     const int keep_max = stable ? INT_MAX : (csize > kFineMin ? csize : kFineMin);
     hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, 256)), dim3(256), 0, s, pos, mass, sel, n, g,
-                       key, rank, cell_start, fp32, keep_max, sp, perm, sel_s, sp2, perm2, sel2);
+                       key, rank, cell_start, fp32, keep_max, sp, perm, sel_s, sp2, perm2, sel2,
+                       big_list);
     return hipGetLastError();
 }
 
-hipError_t launch_big_list(const int *cell_start, const Geom &g, int *big_list, hipStream_t s) {
-    // big_list[0] was zeroed on the stream; it holds at most n / kFineBig ids
-    const long long cells = (long long)g.nt3 * g.ns3;
-    hipLaunchKernelGGL(k_big_list, dim3(grid_for((size_t)cells, 256)), dim3(256), 0, s,
-                       cell_start, cells, big_list);
+hipError_t launch_fine_order(const double4 *sp, const int *perm, const uint8_t *sel,
+                             const int *cell_start, const Geom &g, int *fkey, int *frank,
+                             double4 *sp2, int *perm2, uint8_t *sel2, int n, int csize,
+                             const int *big_list, hipStream_t s) {
+    const int big = std::min(n / kFineBig, 256);
+    const long long med = std::min<long long>((g.nt3 + kFineWaves - 1) / kFineWaves, 1ll << 20);
+    hipLaunchKernelGGL(k_fine_order, dim3((unsigned)(big + med)), dim3(kFineBins), 0, s, sp, perm,
+                       sel, cell_start, g, fkey, frank, sp2, perm2, sel2,
+                       csize > kFineMin ? csize : kFineMin, big, big_list);
     return hipGetLastError();
 }
 
-hipError_t launch_fine_order_medium(const double4 *sp, const int *perm, const uint8_t *sel,
-                                    const int *cell_start, const Geom &g, int *fkey, int *frank,
-                                    double4 *sp2, int *perm2, uint8_t *sel2, int csize,
-                                    hipStream_t s) {
-    long long grid = std::min<long long>((g.nt3 + kFineWaves - 1) / kFineWaves, 1ll << 20);
-    hipLaunchKernelGGL(k_fine_order, dim3((unsigned)grid), dim3(kFineWaves * kWave), 0, s, sp,
-                       perm, sel, cell_start, g, fkey, frank, sp2, perm2, sel2,
-                       csize > kFineMin ? csize : kFineMin, (int *)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_fine_order_big(const double4 *sp, const int *perm, const uint8_t *sel,
-                                 const int *cell_start, const Geom &g, int *fkey, int *frank,
-                                 double4 *sp2, int *perm2, uint8_t *sel2, int n,
-                                 const int *big_list, hipStream_t s) {
-    const int big_grid = std::min(n / kFineBig, 256);
-    if (big_grid > 0)
-        hipLaunchKernelGGL(k_fine_order_big, dim3((unsigned)big_grid), dim3(kFineBins), 0, s, sp,
-                           perm, sel, cell_start, g, fkey, frank, sp2, perm2, sel2, big_list);
-    return hipGetLastError();
-}
-
-hipError_t launch_flags(const uint8_t *sel_s, int n, int n_sub, int kind, const uint8_t *thr_host,
-                        int *flags, hipStream_t s) {
-    size_t total = (size_t)n * n_sub;
-    if (total == 0) return hipSuccess;
+hipError_t launch_receivers(const uint8_t *sel_s, int n, int n_sub, int kind,
+                            const uint8_t *thr_host, const double4 *sp, const int *perm,
+                            int *prefix, double4 *rp, int *rperm, unsigned long long *status,
+                            int *ctr, unsigned long long *stall, hipStream_t s) {
+    const size_t rows = (size_t)n * n_sub;
+    if (rows == 0) return hipSuccess;
     Thresholds thr{};
     if (thr_host)
         for (int k = 0; k < n_sub && k < 64; ++k) thr.t[k] = thr_host[k];
-    hipLaunchKernelGGL(k_flags, dim3(grid_for(total, 256)), dim3(256), 0, s, sel_s, n, n_sub, kind,
-                       thr, flags);
+    hipLaunchKernelGGL(k_receivers, dim3(grid_for(rows, kRecvTile)), dim3(kRecvThreads), 0, s, sel_s,
+                       n, n_sub, kind, thr, sp, perm, prefix, rp, rperm, status, ctr, stall);
     return hipGetLastError();
 }
 
-// Three device counts into host-visible (pinned) memory: one launch instead
-// of a copy per value; read after the stream has been synchronised.
-__global__ void k_totals(const int *a, const int *b, const int *c, int *out) {
-    if (threadIdx.x == 0) {
-        out[0] = *a;
-        out[1] = *b;
-        out[2] = *c;
-    }
+static bool plan_big(int n_sub, const Geom &g) { return (long long)n_sub * g.nt3 > kPlanBigFrom; }
+
+size_t receivers_status_needed(size_t rows) { return (rows + kRecvTile - 1) / kRecvTile; }
+
+size_t plan_status_needed(int n_sub, const Geom &g) {
+    const size_t per = plan_big(n_sub, g) ? kPlanThreadsBig : 64;
+    return ((size_t)n_sub * g.nt3 + per - 1) / per;
 }
 
-hipError_t launch_totals(const int *a, const int *b, const int *c, int *host_out,
-                         hipStream_t s) {
-    hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, s, a, b, c, host_out);
-    return hipGetLastError();
-}
-
-hipError_t launch_compact(const int *scan, int n, int n_sub, int *act_pos, hipStream_t s) {
-    size_t total = (size_t)n * n_sub;
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_compact, dim3(grid_for(total, 256)), dim3(256), 0, s, scan, n, n_sub,
-                       act_pos);
-    return hipGetLastError();
-}
-
-hipError_t launch_cluster_count(const int *cs, const int *scan, int n, int n_sub, const Geom &g,
-                                int csize, int *ncl, hipStream_t s) {
-    size_t total = (size_t)n_sub * g.nt3;
-    hipLaunchKernelGGL(k_cluster_count, dim3(grid_for(total, 256)), dim3(256), 0, s, cs, scan, n,
-                       n_sub, g, csize, ncl);
-    return hipGetLastError();
-}
-
-hipError_t launch_cluster_write(const int *cs, const int *scan, const int *cl_off, int n,
-                                int n_sub, const Geom &g, int csize, Cluster *clusters,
-                                hipStream_t s) {
-    size_t total = (size_t)n_sub * g.nt3;
-    hipLaunchKernelGGL(k_cluster_write, dim3(grid_for(total, 256)), dim3(256), 0, s, cs, scan, n,
-                       n_sub, g, csize, cl_off, clusters);
-    return hipGetLastError();
-}
-
-hipError_t launch_item_count(const Cluster *clusters, const int *n_clusters_dev, int bound,
-                             const int *cs, const Geom &g, int target, int half, int *item_cnt,
-                             hipStream_t s) {
-    if (bound == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_item_count, dim3(grid_for(bound, 128)), dim3(128), 0, s, clusters,
-                       n_clusters_dev, bound, cs, g, target, half, item_cnt);
+hipError_t launch_plan(const PlanArgs &p, const Geom &g, hipStream_t s) {
+    const unsigned grid = (unsigned)plan_status_needed(p.n_sub, g);
+    if (plan_big(p.n_sub, g))
+        hipLaunchKernelGGL((p.half ? k_plan<true, kPlanThreadsBig, kPlanThreadsBig>
+                                   : k_plan<false, kPlanThreadsBig, kPlanThreadsBig>),
+                           dim3(grid), dim3(kPlanThreadsBig), 0, s, p, g);
+    else
+        hipLaunchKernelGGL((p.half ? k_plan<true, 64, kPlanThreads> : k_plan<false, 64, kPlanThreads>),
+                           dim3(grid), dim3(kPlanThreads), 0, s, p, g);
     return hipGetLastError();
 }
 
 hipError_t launch_item_write(const Cluster *clusters, const int *n_clusters_dev, int bound,
                              const int *cs, const Geom &g, int target, int half,
-                             const int *item_off, Item *items, const int *tot_recv,
-                             const int *tot_items, int *host_tot, hipStream_t s) {
-    if (bound == 0 && !host_tot) return hipSuccess;
-    hipLaunchKernelGGL(k_item_write, dim3(grid_for(bound, 128)), dim3(128), 0, s, clusters,
-                       n_clusters_dev, bound, cs, g, target, half, item_off, items, tot_recv,
-                       tot_items, host_tot);
+                             const int *item_off, Item *items, hipStream_t s) {
+    if (bound == 0) return hipSuccess;
+    hipLaunchKernelGGL(half ? k_item_write<true> : k_item_write<false>,
+                       dim3(grid_for(bound, 128)), dim3(128), 0, s, clusters, n_clusters_dev, cs, g,
+                       target, item_off, items);
     return hipGetLastError();
 }
 
@@ -1054,14 +1136,6 @@ hipError_t launch_tile_hist(const int *cell_start, const Geom &g, int *hist32, h
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, hist32, 0, (size_t)32);
     hipLaunchKernelGGL(k_tile_hist, dim3(grid_for((size_t)g.nt3, 256)), dim3(256), 0, s,
                        cell_start, g, hist32);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_weights(const double *grad_acc, const uint8_t *sel_s, const int *perm,
-                                 int n, int fp32, double4 *wa, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_weights, dim3(grid_for(n, 256)), dim3(256), 0, s, grad_acc, sel_s,
-                       perm, n, fp32, wa);
     return hipGetLastError();
 }
 
