@@ -835,8 +835,8 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     }
     // every resident block (the kernels read the item count and size their
     // queue claims on the device; blocks without work leave at once)
-    long long grid = (long long)h->n_cu * bpc;
-    if (grid < 1) grid = 1;
+    // a multiple of the XCD count: the waves' first claims count on it
+    const long long grid = std::max<long long>((long long)h->n_cu * bpc / kXcds * kXcds, kXcds);
     if (h->timing) P3M_HIP(hipEventRecord(h->ev[1], s));
     if (mutual) P3M_HIP(launch_pairs_mutual(a, r.backward, !fp32, (int)grid, s));
     else P3M_HIP(launch_pairs(mode, screen, shape, a, (int)grid, s));

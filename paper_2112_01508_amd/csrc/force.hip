@@ -739,47 +739,102 @@ __device__ inline double group_sum(double v, int lane, int grp, int cnt, int G) 
 // Next work item for this wave.  Items are cut into kXcds contiguous chunks
 // (the item list follows the tile order, so a chunk is a compact region of
 // the box); the workgroups of XCD x (blockIdx % kXcds, the round-robin
-// dispatch order) draw from chunk x through its own counter, so that XCD's
-// L2 serves a compact set of suppliers, and steal from the other chunks once
-// theirs is empty.  A wave claims a.batch consecutive items per atomic: the
-// counters are device-wide, and one atomic per item would serialise on them.
-// Returns -1 when every chunk is exhausted.
+// dispatch order) draw from chunk x, so that XCD's L2 serves a compact set of
+// suppliers, and steal from the other chunks once theirs is empty.  A wave's
+// first claim is its place among the waves of its XCD; the later ones come
+// from the chunk's counter, which counts from behind the first claims.  A
+// claim takes `batch` consecutive items: the counters are device-wide, and one
+// atomic per item would serialise on them.  A launch with fewer items than
+// waves touches no counter at all (with a counter for every claim each of the
+// 4096 or 6144 waves ran through all eight, which cost such a launch about
+// 20 us).  Returns -1 when every chunk is exhausted.
 struct ItemCursor {
     int cur = 0, end = 0;   // claimed items [cur, end)
-    int victim = 0;         // chunks tried so far, from the home chunk on
+    int victim = -1;        // chunks tried so far, from the home chunk on (-1: first claim open)
 };
 
-// The launch's item count (read on the device) and the items a wave claims
-// per queue atomic: about 32 claims per wave, at most 8 items each.
+// The launch's item count (read on the device), the items a wave claims at
+// once (about 32 claims per wave, at most 8 items each) and the items the
+// first claims of an XCD's waves take.
 struct ItemQueue {
     int n;
     int batch;
+    int first;
 };
 __device__ inline ItemQueue item_queue(const PairArgs &a) {
     const int n = __builtin_amdgcn_readfirstlane(*a.n_items_dev);
-    const long long waves = (long long)gridDim.x * (blockDim.x / kWave);
+    const int nw = blockDim.x / kWave;
+    const long long waves = (long long)gridDim.x * nw;
     const long long b = (long long)n / (waves * 32);
-    return ItemQueue{n, (int)(b < 1 ? 1 : (b > 8 ? 8 : b))};
+    const int batch = (int)(b < 1 ? 1 : (b > 8 ? 8 : b));
+    // the grid is a multiple of kXcds blocks (launch_pairs)
+    return ItemQueue{n, batch, (int)(gridDim.x / kXcds) * nw * batch};
 }
 
 __device__ inline int next_item(const PairArgs &a, const ItemQueue &iq, int lane, ItemCursor &q) {
     if (q.cur < q.end) return q.cur++;
     const int home = (int)(blockIdx.x % kXcds);
+    if (q.victim < 0) {
+        q.victim = 0;
+        const int c0 = (int)((long long)iq.n * home / kXcds);
+        const int c1 = (int)((long long)iq.n * (home + 1) / kXcds);
+        const int rank = __builtin_amdgcn_readfirstlane(
+            (int)(blockIdx.x / kXcds) * (int)(blockDim.x / kWave) + (int)(threadIdx.x / kWave));
+        const int at = c0 + rank * iq.batch;
+        if (at < c1) {
+            q.cur = at;
+            q.end = min(at + iq.batch, c1);
+            return q.cur++;
+        }
+    }
     while (q.victim < kXcds) {
         const int x = (home + q.victim) % kXcds;
-        const int c0 = (int)((long long)iq.n * x / kXcds);
+        const int c0 = (int)((long long)iq.n * x / kXcds) + iq.first;
         const int c1 = (int)((long long)iq.n * (x + 1) / kXcds);
-        int got = 0;
-        if (lane == 0) got = atomicAdd(a.queue + x * kQueueStride, iq.batch);
-        got = __builtin_amdgcn_readfirstlane(got);
-        if (c0 + got < c1) {
-            q.cur = c0 + got;
-            q.end = min(c0 + got + iq.batch, c1);
-            return q.cur++;
+        if (c0 < c1) {
+            int got = 0;
+            if (lane == 0) got = atomicAdd(a.queue + x * kQueueStride, iq.batch);
+            got = __builtin_amdgcn_readfirstlane(got);
+            if (c0 + got < c1) {
+                q.cur = c0 + got;
+                q.end = min(c0 + got + iq.batch, c1);
+                return q.cur++;
+            }
         }
         ++q.victim;
     }
     return -1;
+}
+
+// The waves' statistics, summed over the block before they go to the block's
+// copy of the counters (one atomic per block and value: with one per wave,
+// launches of a few thousand items queued on the eight lines at their end).
+// Every wave of the block calls it once, after its last item.
+__device__ __forceinline__ void add_counts(const PairArgs &a, int lane, unsigned long long pairs,
+                                           unsigned long long cand, unsigned long long steps,
+                                           unsigned long long screened, unsigned long long rare) {
+    constexpr int NW = kForceBlock / kWave;
+    __shared__ unsigned long long sums[NW][5];
+    if (lane == 0) {
+        unsigned long long *v = sums[threadIdx.x / kWave];
+        v[0] = pairs;
+        v[1] = cand;
+        v[2] = steps;
+        v[3] = screened;
+        v[4] = rare;
+    }
+    __syncthreads();
+    if (threadIdx.x >= 5) return;
+    unsigned long long t = 0;
+    for (int w = 0; w < NW; ++w) t += sums[w][threadIdx.x];
+    if (t == 0) return;
+    Counters *k = a.counters + (blockIdx.x % kCounterCopies) * kCounterStride;
+    unsigned long long *dst = threadIdx.x == 0   ? &k->interactions
+                              : threadIdx.x == 1 ? &k->candidates
+                              : threadIdx.x == 2 ? &k->steps
+                              : threadIdx.x == 3 ? &k->screened
+                                                 : &k->rare;
+    atomicAdd(dst, t);
 }
 
 template <int SG, int CAP, class Body>
@@ -920,13 +975,7 @@ void k_pairs(PairArgs a) {
     unsigned long long tot = (unsigned long long)wc.n_lane;
     for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, kWave);
     tot += wc.n_ok;
-    if (lane == 0 && a.counters && wc.steps + wc.screened + wc.cand + tot > 0) {
-        Counters *k = a.counters + (blockIdx.x % kCounterCopies) * kCounterStride;
-        atomicAdd(&k->interactions, tot);
-        atomicAdd(&k->candidates, wc.cand);
-        atomicAdd(&k->steps, wc.steps);
-        atomicAdd(&k->screened, wc.screened);
-    }
+    add_counts(a, lane, tot, wc.cand, wc.steps, wc.screened, 0);
 }
 
 // ---- pairs evaluated once for both partners -----------------------------------
@@ -1705,13 +1754,7 @@ void k_pairs_mutual(PairArgs a) {
         mutual_item<RMAX, UNIT, KIND>(a, item, cl, cnt, begin, lane, ring_pos[w], ring_idx[w],
                                      ring_wt[BWD ? w : 0], tally);
     }
-    if (lane == 0 && a.counters && tally.pairs + tally.steps + tally.screened + tally.rare > 0) {
-        Counters *k = a.counters + (blockIdx.x % kCounterCopies) * kCounterStride;
-        atomicAdd(&k->interactions, tally.pairs);
-        atomicAdd(&k->steps, tally.steps);
-        atomicAdd(&k->screened, tally.screened);
-        atomicAdd(&k->rare, tally.rare);
-    }
+    add_counts(a, lane, tally.pairs, 0, tally.steps, tally.screened, tally.rare);
 }
 
 // acc_out[3 perm[p] + c] = sums[c n + p]
