@@ -451,13 +451,8 @@ int tiles_per_dim(double box, double r_cut) {
     return nt < 3 ? 3 : nt;
 }
 
-int pick_subtiles(int nt, int64_t n, int requested) {
-    int ns = requested;
-    if (ns <= 0) {
-        // default before tuning: finer subtiles when tiles hold more particles
-        double per_tile = (double)n / ((double)nt * nt * nt);
-        ns = per_tile > 64 ? 4 : (per_tile > 8 ? 3 : 2);
-    }
+int pick_subtiles(int nt, int requested) {
+    int ns = requested > 0 ? requested : 1;
     while (ns > 1 && (double)nt * ns * nt * ns * nt * ns > 2.0e9) --ns;
     return ns;
 }
@@ -520,9 +515,6 @@ struct Request {
     int force_screen;        // 0: not forced, 1: screening off, 2: on
 };
 
-// Default layout before tuning: full 64-receiver clusters without screening.
-constexpr int kDefaultCsize = 64;
-constexpr int kDefaultScreen = 0;
 // screen == kScreenMutual: all-active FP32 forward calls evaluate each pair
 // once for both partners (other calls screen)
 constexpr int kScreenMutual = 2;
@@ -532,6 +524,46 @@ bool valid_csize(int c) { return c == 8 || c == 16 || c == 32 || c == 64; }
 // B-spline softening length per Plummer-equivalent one (section 2.1.1, below
 // eq. bspline_force: eps_B = 2.8 eps).
 constexpr double kBsplinePerPlummer = 2.8;
+
+// Layout of a call that no configuration and no tuning decides: screened
+// clusters, one subtile per tile (finer ones cost cull entries and drop no
+// supplier that the screen would not; 1 to 5 % slower at every size measured).
+//   - Every particle a receiver, FP64: each pair once for both partners,
+//     clusters of 16, from 8192 particles on (2^21 clustered: 3.56 ms per call
+//     against 4.20 ms screened and 5.94 ms for 64-receiver clusters that walk
+//     their suppliers directly; 32768: 0.083 / 0.092 / 0.19 ms).  Below that
+//     the extra launch that writes its sums out costs as much as it saves
+//     (4096: 0.052 against 0.050 ms).
+//   - FP32 stays on the ordered kernels, which take the separation in FP64;
+//     clusters of 32 (2^21: 2.57 ms, of 16 2.63 ms, of 64 directly 4.19 ms).
+//     The adjoint, whose list entries are larger, takes 16 (2^21 FP32: 4.42
+//     against 4.60 ms).
+//   - Receivers under a mask are sparse, so clusters of 8 (a fifth active of
+//     2^21, FP32: 1.15 ms, of 64 directly 2.50 ms; a fiftieth: 0.50, of 16
+//     0.56, of 64 directly 1.14 ms); nested rung subsets, dense and sparse in
+//     one launch, 32.
+//   - Items of about 128 candidates below 2^14 particles, where one item per
+//     wave leaves the GPU half empty (4096: 0.050 ms; items of 512: 0.06 to
+//     0.08 ms), growing with the set so that the items stay a few per wave
+//     (300007 FP32: 0.293 ms at 1024, 0.339 at 256; 2^21: 2.57 ms at 4096,
+//     2.70 at 512).
+struct Layout {
+    int target, csize, screen;
+};
+Layout default_layout(int64_t n, bool fp32, bool backward, int sel_kind, bool mutual_ok) {
+    Layout l;
+    l.screen = !fp32 && mutual_ok && n >= 8192 ? kScreenMutual : 1;
+    const bool masked = !backward && sel_kind == SEL_MASK;
+    if (l.screen == kScreenMutual) l.csize = 16;
+    else if (masked) l.csize = 8;
+    else if (!backward && sel_kind == SEL_RUNG) l.csize = 32;
+    else l.csize = fp32 && !backward && n >= 8192 ? 32 : 16;
+    if (n < (1 << 14)) l.target = 128;
+    else if (l.screen == kScreenMutual) l.target = (int)std::min<int64_t>(std::max<int64_t>(n >> 10, 512), 4096);
+    else if (n < (1 << 16)) l.target = 256;
+    else l.target = (int)std::min<int64_t>(std::max<int64_t>(n >> 9, 1024), 4096);
+    return l;
+}
 
 int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     hipStream_t s = r.stream;
@@ -588,10 +620,14 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     if (r.force_target > 0) target = r.force_target;
     if (r.force_csize > 0) csize = r.force_csize;
     if (r.force_screen > 0) screen = r.force_screen - 1;
-    ns = pick_subtiles(nt, r.n, ns);
-    if (target <= 0) target = 1024;
-    if (!valid_csize(csize)) csize = kDefaultCsize;
-    if (screen < 0) screen = kDefaultScreen;
+    // the fixed workspace holds the mutual kernel's sums beside everything
+    // else it held for a call up to half its particle limit
+    const Layout def = default_layout(r.n, fp32, r.backward, r.sel_kind,
+                                      mutual_ok && !(w.base && r.n > kNoAllocMaxN / 2));
+    ns = pick_subtiles(nt, ns);
+    if (target <= 0) target = def.target;
+    if (!valid_csize(csize)) csize = screen == kScreenMutual ? std::max(def.csize, 16) : def.csize;
+    if (screen < 0) screen = def.screen == kScreenMutual && csize < 16 ? 1 : def.screen;
     const Geom g = make_geom(r.box, r.x_s, r.r_cut, nt, ns, eps_b);
     const size_t ncells = (size_t)g.nt3 * g.ns3;
     // other calls with this layout take the screened kernel
@@ -667,7 +703,14 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     // the count, unless that bound passes kItemBoundBytes (or what is left of
     // the fixed workspace), or in the deterministic mode, whose partial slots
     // are per item: then the host waits for the count (below)
-    const size_t item_bound = cl_bound * (size_t)plan_items_bound(g.ns3, mutual ? 1 : 0);
+    // Dense tiles of one subtile are split in small sets, where the array
+    // still holds the items without asking for their number.
+    size_t item_bound = cl_bound * (size_t)plan_items_bound(g.ns3, mutual ? 1 : 0);
+    const size_t split_bound =
+        item_bound + (size_t)n_sub * (size_t)split_items_bound(n, csize, target);
+    const size_t room = w.base ? (w.size - w.used) / sizeof(Item) : kItemBoundBytes / sizeof(Item);
+    const int split = g.ns3 == 1 && n <= kSplitMax && split_bound + 16 <= room ? 1 : 0;
+    if (split) item_bound = split_bound;
     bool wait_count = det || item_bound * sizeof(Item) > kItemBoundBytes ||
                       item_bound > (size_t)INT_MAX;
     if (!wait_count && w.base && w.used + item_bound * sizeof(Item) + 256 > w.size)
@@ -762,6 +805,7 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
         pa.csize = csize;
         pa.target = target;
         pa.half = mutual ? 1 : 0;
+        pa.split = split;
         pa.clusters = clusters;
         pa.items = wait_count ? nullptr : (Item *)w.items.p;
         pa.item_off = item_off;
@@ -781,7 +825,7 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
         if (det && (rc = take(h, w, w.partials, sizeof(double) * 3 * (size_t)csize * count, s)))
             return rc;
         P3M_HIP(launch_item_write(clusters, n_clusters, (int)cl_bound, cells, g, target,
-                                  mutual ? 1 : 0, item_off, (Item *)w.items.p, s));
+                                  mutual ? 1 : 0, split, item_off, (Item *)w.items.p, s));
     }
     P3M_HIP(launch_cluster_finish(clusters, n_clusters, cl_bound, csize, rp, r.grad_acc, sel_s, perm,
                                   fp32 ? 1 : 0, wa, s));
@@ -1229,7 +1273,7 @@ int tune(p3m_sr_context *h, Request &r, const TuneKey &key, int level,
         }
     } guard{e0, e1};
     float best = 1e30f;
-    TuneVal best_v{pick_subtiles(key.nt, r.n, 0), 1024, kDefaultCsize, kDefaultScreen};
+    TuneVal best_v{1, 1024, 64, 0};
     // every candidate's time per call, for the final re-timing of the fastest
     std::vector<std::pair<float, TuneVal>> seen;
     auto time_layout = [&](const TuneVal &v, int nrep, float *per_call) -> int {
@@ -1267,7 +1311,7 @@ int tune(p3m_sr_context *h, Request &r, const TuneKey &key, int level,
         return P3M_OK;
     };
     for (int ns : ns_list) {
-        if (pick_subtiles(key.nt, r.n, ns) != ns) continue;
+        if (pick_subtiles(key.nt, ns) != ns) continue;
         for (const auto &l : layouts)
             for (int tg : targets)
                 if ((rc = trial(TuneVal{ns, tg, l.first, l.second}))) return rc;

@@ -275,9 +275,12 @@ struct BwdF32 {
                                            const PairArgs &a) {
         const Geom &g = a.g;
         const float muj = mu_f32(pj.w);
-        float vx = muj * wkx - muk * wj.x;
-        float vy = muj * wky - muk * wj.y;
-        float vz = muj * wkz - muk * wj.z;
+        // the FP32 contractions are spelled out: left to the compiler they
+        // differed between the loops this body is inlined in, and with them a
+        // pair's rounding between layouts
+        float vx = fmaf(muj, wkx, -(muk * wj.x));
+        float vy = fmaf(muj, wky, -(muk * wj.y));
+        float vz = fmaf(muj, wkz, -(muk * wj.z));
         if (SOFT && r2 < g.eps_b2) {
             const double ri = rsqrt_pos(r2);
             const double ri2 = ri * ri;
@@ -301,7 +304,7 @@ struct BwdF32 {
         float phi = gu * ri2 * ri;
         float c = ri2 * fmaf(3.0f, phi, g.kbf * e);
         float fx = (float)dx, fy = (float)dy, fz = (float)dz;
-        float rv = fx * vx + fy * vy + fz * vz;
+        float rv = fmaf(fz, vz, fmaf(fx, vx, fy * vy));
         float crv = c * rv;
         ax -= (double)fmaf(phi, vx, -crv * fx);
         ay -= (double)fmaf(phi, vy, -crv * fy);
@@ -660,7 +663,10 @@ __device__ __forceinline__ void walk_item(Visit &v, const Item &item, const Clus
     const double *lo = cl.lo, *hi = cl.hi;
     const int tx = cl.tile / (g.nt * g.nt), ty = (cl.tile / g.nt) % g.nt, tz = cl.tile % g.nt;
     const int t0 = item.tiles & 0xff, t1 = (item.tiles >> 8) & 0xff;
-    const int s0 = item.subs & 0xffff, s1 = (item.subs >> 16) & 0xffff;
+    // kItemPart: run `part` of `parts` equal runs of the tile's records
+    const bool split = (item.sole & kItemPart) != 0;
+    const int part = item.subs & 0xffff, parts = (item.subs >> 16) & 0xffff;
+    const int s0 = split ? 0 : part, s1 = split ? 1 : parts;
     const int S = s1 - s0;                 // subtiles of each tile in this item
     const int E = (t1 - t0) * S;           // (tile, subtile) entries
     const int nss = g.ns * g.ns;
@@ -716,8 +722,13 @@ __device__ __forceinline__ void walk_item(Visit &v, const Item &item, const Clus
                 const int ra = __builtin_ctzll(m);
                 const unsigned long long rest = ~(m >> ra);
                 const int rb = rest ? ra + __builtin_ctzll(rest) : kWave;   // run [ra, rb)
-                const int j0 = __builtin_amdgcn_readlane(cst, ra);
-                const int j1 = __builtin_amdgcn_readlane(cen, rb - 1);
+                int j0 = __builtin_amdgcn_readlane(cst, ra);
+                int j1 = __builtin_amdgcn_readlane(cen, rb - 1);
+                if (split) {
+                    const long long len = j1 - j0;
+                    j1 = j0 + (int)(len * (part + 1) / parts);
+                    j0 += (int)(len * part / parts);
+                }
                 m = rb >= kWave ? 0ull : (m & (~0ull << rb));
                 if (j1 > j0) v.run(j0, j1);
             }

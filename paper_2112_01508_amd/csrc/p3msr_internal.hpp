@@ -82,12 +82,14 @@ struct Cluster {
 struct Item {
     int cluster;
     int tiles;    // t0 | t1 << 8
-    int subs;     // s0 | s1 << 16
+    int subs;     // s0 | s1 << 16; kItemPart: part | parts << 16
     int sole;     // kItemSole: the only item of its cluster (its sums are stored, not
-                  // added); kItemFirst: the cluster's first item
+                  // added); kItemFirst: the cluster's first item; kItemPart: one of
+                  // `parts` equal runs of the records of one tile of one subtile
 };
 constexpr int kItemSole = 1;
 constexpr int kItemFirst = 2;
+constexpr int kItemPart = 4;
 
 struct Counters {
     unsigned long long interactions;
@@ -113,9 +115,17 @@ enum SelKind { SEL_ALL = 0, SEL_MASK = 1, SEL_RUNG = 2 };
 
 // Greedy grouping of the 27 neighbour tiles into items of about `target`
 // supplier candidates (before subtile culling); a tile holding more than
-// `target` particles is split by subtile ranges.  At most 2 items per stencil
-// tile plus one with one subtile per tile (a flush and the tile itself), at
-// most 1 + ns^3 per tile plus one otherwise (plan_items_bound).
+// `target` particles is split by subtile ranges, or, where a tile is one
+// subtile and `split` is set, into runs of about `target` of its records.
+// Without a split, at most 2 items per stencil tile plus one with one subtile
+// per tile (a flush and the tile itself), at most 1 + ns^3 per tile plus one
+// otherwise (plan_items_bound).  Splits add less than w / target items per
+// cluster and tile of w particles, and a tile is in the stencils of at most
+// 27 tiles, whose clusters number at most 27 + n / csize (split_items_bound).
+// They are for small sets (kSplitMax): a halo that holds a good part of one
+// has too few clusters to fill the GPU, and one of its items would walk the
+// whole halo (120000 particles, half of them in one tile, FP32: 8.9 ms per
+// call without, 2.9 ms with); in larger sets other clusters fill the GPU.
 //
 // HALF (pairs evaluated once, for both partners): only the upper half of the
 // stencil, t = 13 .. 26, whose periodic mirror images are the lower half; in
@@ -127,6 +137,12 @@ inline long long plan_items_bound(int ns3, int half) {
     const long long tiles = half ? 14 : 27;
     return tiles * (ns3 == 1 ? 2 : 1 + ns3) + 2;
 }
+
+inline long long split_items_bound(long long n, int csize, int target) {
+    return (n / target) * (27 + n / csize);
+}
+constexpr int kSplitMax = 1 << 20;   // particles
+constexpr int kSplitParts = 1 << 14; // runs per tile
 
 // Particles of each stencil tile of the cluster [begin, begin + count) of
 // `tile` that the plan counts.  All loads are issued before any is used: the
@@ -152,23 +168,29 @@ __device__ __forceinline__ void plan_weights(int tile, int end, const int *__res
     for (int t = T0; t < 27; ++t) w[t] = hi[t] - lo[t];
 }
 
-// The items of one cluster in order, each handed to emit(k, t0, t1, s0, s1);
-// returns their number.
+// The items of one cluster in order, each handed to emit(k, t0, t1, s0, s1,
+// kItemPart or 0); returns their number.
 template <bool HALF, class Emit>
-__device__ __forceinline__ int plan_items(const int (&w)[27], int target, int ns3, Emit emit) {
+__device__ __forceinline__ int plan_items(const int (&w)[27], int target, int ns3, int split,
+                                          Emit emit) {
     constexpr int T0 = HALF ? 13 : 0;
     int n = 0, acc = 0, t0 = T0;
 #pragma unroll
     for (int t = T0; t < 27; ++t) {
         if (w[t] > target) {
-            if (acc > 0) emit(n++, t0, t, 0, ns3);
-            const int parts = min((w[t] + target - 1) / target, ns3);
-            for (int q = 0; q < parts; ++q)
-                emit(n++, t, t + 1, q * ns3 / parts, (q + 1) * ns3 / parts);
+            if (acc > 0) emit(n++, t0, t, 0, ns3, 0);
+            if (split) {
+                const int parts = min(w[t] / target, kSplitParts);
+                for (int q = 0; q < parts; ++q) emit(n++, t, t + 1, q, parts, kItemPart);
+            } else {
+                const int parts = min((w[t] + target - 1) / target, ns3);
+                for (int q = 0; q < parts; ++q)
+                    emit(n++, t, t + 1, q * ns3 / parts, (q + 1) * ns3 / parts, 0);
+            }
             t0 = t + 1;
             acc = 0;
         } else if (acc + w[t] > target) {
-            emit(n++, t0, t, 0, ns3);
+            emit(n++, t0, t, 0, ns3, 0);
             t0 = t;
             acc = w[t];
         } else {
@@ -176,8 +198,8 @@ __device__ __forceinline__ int plan_items(const int (&w)[27], int target, int ns
             acc += w[t];
         }
     }
-    if (acc > 0) emit(n++, t0, 27, 0, ns3);
-    if (HALF && n == 0) emit(n++, 13, 14, 0, ns3);
+    if (acc > 0) emit(n++, t0, 27, 0, ns3, 0);
+    if (HALF && n == 0) emit(n++, 13, 14, 0, ns3, 0);
     return n;
 }
 
@@ -250,6 +272,7 @@ struct PlanArgs {
     const int *cell_start;
     const int *prefix;      // of launch_receivers; nullptr: every particle a receiver
     int n, n_sub, csize, target, half;
+    int split;              // dense tiles of one subtile into runs of records
     Cluster *clusters;      // tile, subset, begin and count of every cluster
     Item *items;            // nullptr: counted only
     int *item_off;          // nullptr, or the first item of every cluster (and the total)
@@ -264,7 +287,7 @@ hipError_t launch_plan(const PlanArgs &p, const Geom &g, hipStream_t s);
 // every cluster's items at their offsets item_off of launch_plan (for arrays
 // sized after the count is known); at most `bound` clusters
 hipError_t launch_item_write(const Cluster *clusters, const int *n_clusters_dev, int bound,
-                             const int *cell_start, const Geom &g, int target, int half,
+                             const int *cell_start, const Geom &g, int target, int half, int split,
                              const int *item_off, Item *items, hipStream_t s);
 // 32-bin histogram of particles per tile (log2 bins; bin 0: empty tiles),
 // the occupancy signature the autotuner files its results under

@@ -737,14 +737,14 @@ __global__ __launch_bounds__(NT) void k_plan(PlanArgs a, Geom g) {
         cl.begin = beg[lo] + skip;
         cl.count = min(a.csize, num[lo] - skip);
     };
-    auto nothing = [](int, int, int, int, int) {};
+    auto nothing = [](int, int, int, int, int, int) {};
     int mine = 0;
     for (int c = t; c < n_cl; c += NT) {
         Cluster cl;
         locate(c, cl);
         int w[27];
         plan_weights<HALF>(cl.tile, cl.begin + cl.count, a.cell_start, g, w);
-        const int k = plan_items<HALF>(w, a.target, g.ns3, nothing);
+        const int k = plan_items<HALF>(w, a.target, g.ns3, a.split, nothing);
         if (c < kPlanCache) cache[c] = (unsigned short)min(k, 0xffff);
         mine += k;
     }
@@ -781,7 +781,7 @@ __global__ __launch_bounds__(NT) void k_plan(PlanArgs a, Geom g) {
                 make_int4(cl.tile, cl.subset, cl.begin, cl.count);
             plan_weights<HALF>(cl.tile, cl.begin + cl.count, a.cell_start, g, w);
             k = c < kPlanCache ? cache[c] : 0xffff;
-            if (k == 0xffff) k = plan_items<HALF>(w, a.target, g.ns3, nothing);
+            if (k == 0xffff) k = plan_items<HALF>(w, a.target, g.ns3, a.split, nothing);
         }
         int total;
         const int off = it0 + block_exclusive_scan(k, lds, &total);
@@ -790,11 +790,12 @@ __global__ __launch_bounds__(NT) void k_plan(PlanArgs a, Geom g) {
             if (a.items) {
                 const int sole = k == 1 ? kItemSole : 0;
                 Item *out = a.items + off;
-                plan_items<HALF>(w, a.target, g.ns3, [&](int q, int t0, int t1, int s0, int s1) {
-                    *reinterpret_cast<int4 *>(out + q) =
-                        make_int4(cl0 + c, t0 | (t1 << 8), s0 | (s1 << 16),
-                                  sole | (q == 0 ? kItemFirst : 0));
-                });
+                plan_items<HALF>(w, a.target, g.ns3, a.split,
+                                 [&](int q, int t0, int t1, int s0, int s1, int part) {
+                                     *reinterpret_cast<int4 *>(out + q) =
+                                         make_int4(cl0 + c, t0 | (t1 << 8), s0 | (s1 << 16),
+                                                   sole | part | (q == 0 ? kItemFirst : 0));
+                                 });
             }
         }
         it0 += total;
@@ -805,7 +806,7 @@ __global__ __launch_bounds__(NT) void k_plan(PlanArgs a, Geom g) {
 // device.
 template <bool HALF>
 __global__ void k_item_write(const Cluster *__restrict__ clusters, const int *__restrict__ n_cl,
-                             const int *__restrict__ cs, Geom g, int target,
+                             const int *__restrict__ cs, Geom g, int target, int split,
                              const int *__restrict__ item_off, Item *__restrict__ items) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= *n_cl) return;
@@ -814,10 +815,12 @@ __global__ void k_item_write(const Cluster *__restrict__ clusters, const int *__
     const Cluster &cl = clusters[c];
     int w[27];
     plan_weights<HALF>(cl.tile, cl.begin + cl.count, cs, g, w);
-    plan_items<HALF>(w, target, g.ns3, [&](int q, int t0, int t1, int s0, int s1) {
-        *reinterpret_cast<int4 *>(items + off + q) = make_int4(
-            c, t0 | (t1 << 8), s0 | (s1 << 16), sole | (q == 0 ? kItemFirst : 0));
-    });
+    plan_items<HALF>(w, target, g.ns3, split,
+                     [&](int q, int t0, int t1, int s0, int s1, int part) {
+                         *reinterpret_cast<int4 *>(items + off + q) =
+                             make_int4(c, t0 | (t1 << 8), s0 | (s1 << 16),
+                                       sole | part | (q == 0 ? kItemFirst : 0));
+                     });
 }
 
 // Deterministic mode: the sums of every cluster with several items, added
@@ -1113,12 +1116,12 @@ hipError_t launch_plan(const PlanArgs &p, const Geom &g, hipStream_t s) {
 }
 
 hipError_t launch_item_write(const Cluster *clusters, const int *n_clusters_dev, int bound,
-                             const int *cs, const Geom &g, int target, int half,
+                             const int *cs, const Geom &g, int target, int half, int split,
                              const int *item_off, Item *items, hipStream_t s) {
     if (bound == 0) return hipSuccess;
     hipLaunchKernelGGL(half ? k_item_write<true> : k_item_write<false>,
                        dim3(grid_for(bound, 128)), dim3(128), 0, s, clusters, n_clusters_dev, cs, g,
-                       target, item_off, items);
+                       target, split, item_off, items);
     return hipGetLastError();
 }
 
