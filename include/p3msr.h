@@ -115,8 +115,8 @@ typedef struct {
     int64_t n;               /* particles */
     int32_t n_grid;          /* PM grid points per dimension */
     int32_t pad;
-    float ms_sort;           /* counting sort of the particles by CIC node, kernel tables */
-    float ms_deposit;        /* CIC deposit (sparse nodes per brick, dense nodes by atomics) */
+    float ms_sort;           /* counting sort of the particles by bins of CIC nodes, kernel tables */
+    float ms_deposit;        /* CIC deposit (per brick in LDS, runs of dense bins on top) */
     float ms_fft_x_fwd;      /* real-to-half-spectrum pass along x */
     float ms_fft_y_fwd;      /* forward pass along y */
     float ms_fft_z_conv;     /* forward z, kernel multiply, inverse z (one pass) */
@@ -426,10 +426,11 @@ int p3m_sr_get_stats(p3m_sr_handle h, p3m_sr_stats *out);
  * x_s is the P3M acceleration of eq. p3m_gravity (without softening).
  *   n_grid  grid points per dimension: a power of two, 16..1024 (the paper
  *           uses n_grid = 2 cbrt(N) with x_s = 1.25 box / n_grid).
- * All arithmetic is FP64.  The workspace holds 12 n_grid^3 + 16 (n_grid/2+1)
- * n_grid^2 + 56 n bytes (grids, node histogram, particles sorted by node).
- * The deposit adds with FP64 atomics (in LDS for nodes holding at most 8
- * particles, in HBM for denser ones), so results can differ between runs in
+ * All arithmetic is FP64.  The workspace holds 8 n_grid^3 + 16 (n_grid/2+1)
+ * n_grid^2 + n_grid^3 / 128 + 48 n bytes (grids, counts of the 8^3-node bins,
+ * particles sorted by bin).  The deposit adds with FP64 atomics (in LDS, and
+ * in HBM for bins of more than 2048 particles), so results can differ between
+ * runs in
  * the last bits.  Errors: EINVAL for n < 0, box or x_s not positive and
  * finite, n_grid outside the supported set, NULL pos/acc_out with n > 0, or
  * pointers not 8-byte aligned; EUNSUPPORTED for n > 2^31 - 16; ENOMEM; EHIP.

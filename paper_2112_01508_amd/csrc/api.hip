@@ -180,8 +180,9 @@ struct p3m_sr_context {
     hipEvent_t tot_ev = nullptr;   // after the totals of a call reach host memory
     int *host_tot = nullptr;   // pinned: receivers, clusters, items of the current call
     // long-range PM workspace and timing
-    DevBuf pm_real, pm_spec, pm_tab, pm_key, pm_rank, pm_cnt, pm_rec, pm_nkey, pm_perm, pm_recv,
-        pm_bsum, p3m_lr, tune_w, tune_sig;
+    DevBuf pm_real, pm_spec, pm_tab, pm_key, pm_rank, pm_bins, pm_rec, pm_nkey, pm_perm, pm_bsum,
+        p3m_lr, tune_w, tune_sig;
+    unsigned long long *pm_stall = nullptr;   // the bin scan's give-up count (in pm_bins)
     // p3m_force: the long-range half runs on this stream beside the short range
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
@@ -920,16 +921,18 @@ int lr_run(p3m_sr_context *h, const double *pos, const double *mass, const uint8
     if ((rc = ensure(h, h->pm_spec, nh * g * g * 2 * sizeof(double), s))) return rc;
     if ((rc = ensure(h, h->pm_tab, (g / 2) * 2 * sizeof(double) + 2 * g * sizeof(double), s)))
         return rc;
-    const size_t cells = g * g * g;
     const size_t np1 = (size_t)np + 1;
-    if ((rc = ensure(h, h->pm_cnt, (cells + 1) * sizeof(int), s))) return rc;
-    if ((rc = ensure(h, h->pm_bsum, sizeof(int) * scan_block_sums_needed(cells), s))) return rc;
+    const size_t bins = (g / kPmBin) * (g / kPmBin) * (g / kPmBin);
+    if ((rc = ensure(h, h->pm_bins, sizeof(int) * pm_sort_layout(nullptr, n_grid, np).ints, s)))
+        return rc;
+    if ((rc = ensure(h, h->pm_bsum, sizeof(int) * scan_block_sums_needed(bins), s))) return rc;
     if ((rc = ensure(h, h->pm_key, np1 * sizeof(int), s))) return rc;
     if ((rc = ensure(h, h->pm_rank, np1 * sizeof(int), s))) return rc;
     if ((rc = ensure(h, h->pm_rec, np1 * sizeof(double4), s))) return rc;
     if ((rc = ensure(h, h->pm_nkey, np1 * sizeof(int), s))) return rc;
     if ((rc = ensure(h, h->pm_perm, np1 * sizeof(int), s))) return rc;
-    if ((rc = ensure(h, h->pm_recv, np1, s))) return rc;
+    const PmSort ps = pm_sort_layout((int *)h->pm_bins.p, n_grid, np);
+    h->pm_stall = ps.stall;
     h->last_stream = s;
     double2 *tw = (double2 *)h->pm_tab.p;
     double *w1 = (double *)(tw + g / 2);
@@ -943,14 +946,11 @@ int lr_run(p3m_sr_context *h, const double *pos, const double *mass, const uint8
     }
     double4 *rec = (double4 *)h->pm_rec.p;
     int *nkey = (int *)h->pm_nkey.p, *perm = (int *)h->pm_perm.p;
-    uint8_t *recv = (uint8_t *)h->pm_recv.p;
-    P3M_HIP(launch_pm_tables(n_grid, box, x_s, tw, w1, k2, s));
+    P3M_HIP(launch_pm_prepare(n_grid, box, x_s, tw, w1, k2, ps, s));
     P3M_HIP(launch_pm_sort(pos, mass, active, np, n_grid, box, hcell, (int *)h->pm_key.p,
-                           (int *)h->pm_rank.p, (int *)h->pm_cnt.p, (int *)h->pm_bsum.p, rec, nkey,
-                           perm, recv, s));
+                           (int *)h->pm_rank.p, ps, (int *)h->pm_bsum.p, rec, nkey, perm, s));
     if (timing) P3M_HIP(hipEventRecord(h->lr_ev[1], s));
-    P3M_HIP(launch_pm_deposit(rec, nkey, (const int *)h->pm_cnt.p, np, (double *)h->pm_real.p,
-                              n_grid, s));
+    P3M_HIP(launch_pm_deposit(rec, nkey, ps, np, (double *)h->pm_real.p, n_grid, s));
     if (timing) P3M_HIP(hipEventRecord(h->lr_ev[2], s));
     PmArgs a{};
     a.n = n_grid;
@@ -962,8 +962,8 @@ int lr_run(p3m_sr_context *h, const double *pos, const double *mass, const uint8
     a.scale = 4.0 * M_PI / (hcell * hcell * hcell * hcell) / ((double)g * (double)g * (double)g);
     P3M_HIP(launch_pm_fft_chain(a, s, timing ? h->lr_ev + 3 : nullptr));
     if (timing) P3M_HIP(hipEventRecord(h->lr_ev[7], s));
-    P3M_HIP(launch_pm_readout(rec, nkey, perm, recv, np, (const double *)h->pm_real.p, n_grid,
-                              acc_out, s));
+    P3M_HIP(launch_pm_readout(rec, nkey, perm, np, (const double *)h->pm_real.p, n_grid, acc_out,
+                              s));
     if (timing) P3M_HIP(hipEventRecord(h->lr_ev[8], s));
     h->lr_stats = p3m_lr_stats{};
     h->lr_stats.n = np;
@@ -1043,7 +1043,7 @@ int p3m_sr_destroy(p3m_sr_handle h) {
                       &w.msum,    &w.htab,    &w.det_k,    &w.det_v,    &w.det_hist,
                       &w.partials, &w.back,
                       &h->pm_real, &h->pm_spec, &h->pm_tab, &h->pm_key,  &h->pm_rank,
-                      &h->pm_cnt,  &h->pm_rec,  &h->pm_nkey, &h->pm_perm, &h->pm_recv,
+                      &h->pm_bins, &h->pm_rec,  &h->pm_nkey, &h->pm_perm,
                       &h->kdk_acc, &h->kdk_lr,  &h->kdk_tq,  &h->kdk_tnext, &h->kdk_due,
                       &h->kdk_scal, &h->pm_bsum, &h->p3m_lr, &h->tune_w, &h->tune_sig};
     for (DevBuf *b : bufs)
@@ -1676,6 +1676,13 @@ int p3m_lr_get_stats(p3m_sr_handle h, p3m_lr_stats *out) {
         P3M_HIP(hipEventElapsedTime(&st.ms_total, h->lr_ev[0], h->lr_ev[8]));
     } else if (h->lr_stream || st.n > 0) {
         P3M_HIP(hipStreamSynchronize(h->lr_stream));
+    }
+    if (h->pm_stall && st.n > 0) {
+        unsigned long long stalled = 0;
+        P3M_HIP(hipMemcpy(&stalled, h->pm_stall, sizeof(stalled), hipMemcpyDeviceToHost));
+        if (stalled)
+            return set_error(P3M_EHIP, "the bin scan of the last call waited past its poll limit "
+                                       "(its result is not valid)");
     }
     *out = st;
     return P3M_OK;

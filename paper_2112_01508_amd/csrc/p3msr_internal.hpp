@@ -203,6 +203,71 @@ __device__ __forceinline__ int plan_items(const int (&w)[27], int target, int ns
     return n;
 }
 
+// ---- cell counting -----------------------------------------------------------
+
+// Key and rank inside its cell of PPT consecutive-block particles per thread,
+// with one global atomic per distinct cell of a block of kKeysThreads x PPT
+// particles: the block's keys are counted in an LDS hash table first (a dense
+// halo cell's particles, which share blocks, would otherwise hit one counter
+// from every wave that holds any of them, and those atomics serialise on its
+// address).  The global atomics bound the kernels that use it, so larger
+// blocks (more particles sharing a cell) pay off.  key_of(i) >= 0; cell_count
+// zeroed before the launch.
+constexpr int kKeysThreads = 1024;
+
+template <int PPT, class KeyOf>
+__device__ __forceinline__ void block_ranks(int n, int *__restrict__ key, int *__restrict__ rank,
+                                            int *__restrict__ cell_count, KeyOf key_of) {
+    constexpr int kSlots = 2 * kKeysThreads * PPT;   // open addressing, at most half full
+    constexpr int kShift = 32 - __builtin_ctz(kSlots);
+    __shared__ int skey[kSlots];
+    __shared__ int scnt[kSlots];
+    for (int t = threadIdx.x; t < kSlots; t += blockDim.x) {
+        skey[t] = -1;
+        scnt[t] = 0;
+    }
+    __syncthreads();
+    int slot[PPT], local[PPT];
+#pragma unroll
+    for (int p = 0; p < PPT; ++p) {
+        const long long i = ((long long)blockIdx.x * PPT + p) * kKeysThreads + threadIdx.x;
+        slot[p] = -1;
+        local[p] = 0;
+        if (i < n) {
+            const int k = key_of((size_t)i);
+            key[i] = k;
+            // k >= 0 and the table never fills, so the probe ends
+            int sl = (int)(((unsigned)k * 2654435761u) >> kShift);
+            for (;;) {
+                const int old = atomicCAS(&skey[sl], -1, k);
+                if (old == -1 || old == k) break;
+                sl = (sl + 1) & (kSlots - 1);
+            }
+            slot[p] = sl;
+            local[p] = atomicAdd(&scnt[sl], 1);
+        }
+    }
+    __syncthreads();
+    // one global atomic per occupied slot; its base replaces the count
+    for (int t = threadIdx.x; t < kSlots; t += blockDim.x) {
+        const int kk = skey[t];
+        if (kk >= 0) scnt[t] = atomicAdd(&cell_count[kk], scnt[t]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PPT; ++p) {
+        const long long i = ((long long)blockIdx.x * PPT + p) * kKeysThreads + threadIdx.x;
+        if (slot[p] >= 0) rank[i] = scnt[slot[p]] + local[p];
+    }
+}
+
+// Particles per thread: the largest block (more particles per global atomic)
+// that still gives every CU one, 8 from N = 2^21, 1 below 2^19.
+inline int keys_per_thread(int n) {
+    const size_t per_cu = (size_t)n / (256 * kKeysThreads);
+    return per_cu >= 8 ? 8 : per_cu >= 4 ? 4 : per_cu >= 2 ? 2 : 1;
+}
+
 // ---- launchers (host functions defined in the .hip files) -----------------
 
 // sort.hip
@@ -378,25 +443,38 @@ struct PmArgs {
     const double *w1, *k2;
     double scale;
 };
-hipError_t launch_pm_tables(int n, double box, double x_s, double2 *tw, double *w1, double *k2,
-                            hipStream_t s);
-// sort: key/rank n_part ints, count n^3 + 1 ints (scanned in place into the
-// first sorted index of each node), bsum scan block sums;
-// rec (CIC fractions, mu), nkey, perm, recv n_part entries in node order
+// The particles are sorted by bins of kPmBin^3 lower CIC nodes.  bins: an int
+// array of pm_sort_ints(n, n_part) entries (16-byte aligned) for the bins'
+// counts, scanned in place into the first sorted index of each bin, and the
+// sort's small counters and lists.
+constexpr int kPmBin = 8;
+struct PmSort {
+    int *start;                   // (n / kPmBin)^3 + 1
+    int *over;                    // runs of dense bins: their number, then (bin, first) pairs
+    unsigned long long *status;   // the scan's look-back words
+    unsigned long long *stall;
+    int *ctr;
+    size_t ints;                  // the array's length
+};
+PmSort pm_sort_layout(int *bins, int n, int n_part);
+// twiddles, kernel tables, and the cleared sort array
+hipError_t launch_pm_prepare(int n, double box, double x_s, double2 *tw, double *w1, double *k2,
+                             const PmSort &ps, hipStream_t s);
+// key/rank: n_part ints of scratch; bsum: scan block sums; rec (CIC fractions,
+// mu), nkey (the lower node) and perm (the particle, ~particle where it
+// receives nothing) n_part entries in bin order
 hipError_t launch_pm_sort(const double *pos, const double *mass, const uint8_t *active,
                           int n_part, int n, double box, double h, int *key, int *rank,
-                          int *count, int *bsum, double4 *rec, int *nkey, int *perm,
-                          uint8_t *recv, hipStream_t s);
-// rho (n^3, fully written) from the node-sorted records; start: the node
-// starts of the sort (n^3 + 1 entries)
-hipError_t launch_pm_deposit(const double4 *rec, const int *nkey, const int *start, int n_part,
+                          const PmSort &ps, int *bsum, double4 *rec, int *nkey, int *perm,
+                          hipStream_t s);
+// rho (n^3, fully written) from the sorted records
+hipError_t launch_pm_deposit(const double4 *rec, const int *nkey, const PmSort &ps, int n_part,
                              double *rho, int n, hipStream_t s);
 // ev (optional): 4 events recorded after the x, y and z passes and the y
 // inverse pass
 hipError_t launch_pm_fft_chain(const PmArgs &a, hipStream_t s, hipEvent_t *ev);
-hipError_t launch_pm_readout(const double4 *rec, const int *nkey, const int *perm,
-                             const uint8_t *recv, int n_part, const double *phi, int n,
-                             double *acc, hipStream_t s);
+hipError_t launch_pm_readout(const double4 *rec, const int *nkey, const int *perm, int n_part,
+                             const double *phi, int n, double *acc, hipStream_t s);
 // pair-kernel workgroups resident per CU for the variant launch_pairs would run
 int pairs_blocks_per_cu(int mode, int screen, int tab, int csize, int unit_mass, int soft);
 // All-active FP32 forward (bwd: the FP32 adjoint, every particle a receiver,

@@ -2,10 +2,10 @@
 // upper half of eq. p3m_gravity, which runs the PM steps of eq. pm_method
 // with the long-range kernel exp(-x_s^2 k^2) / k^2 of eq. ewald_potential:
 //
-//   sort       counting sort of the particles by lower CIC node
+//   sort       counting sort of the particles by bins of 8^3 lower CIC nodes
 //   deposit    rho_m = sum_j mu_j W(x_m - x_j), CIC weights (eq. W_CIC),
-//              cell-centred nodes x_m = h (m + 1/2); runs of one node inside a
-//              wavefront are summed first, then FP64 atomics
+//              cell-centred nodes x_m = h (m + 1/2); added in LDS brick by
+//              brick, each brick stored once
 //   x forward  real lines two at a time as one complex line, radix-2 FFT in
 //              LDS, split into the two half spectra (kx = 0 .. n/2)
 //   y forward  strided complex FFTs over tiles of adjacent kx columns
@@ -63,214 +63,195 @@ __device__ __forceinline__ int cic_node(double x, double box, double h, int n, d
     return ((int)i0 + n) & (n - 1);
 }
 
-// Counting sort of the particles by their lower CIC node (key (z n + y) n + x):
-// rank inside the node from an atomic counter, then a scatter to
-// start[key] + rank.  The sorted record holds the CIC fractions and mu, so the
-// deposit and the readout need neither the positions nor a division.  (Nodes
-// are too fine for lanes of a wave to share one often: grouping the lanes by
-// node before the atomic, as the cell count does, made this kernel slower.)
-__global__ void k_pm_keys(const double *__restrict__ pos, int n_part, int n, double box, double h,
-                          int *__restrict__ key, int *__restrict__ rank,
-                          int *__restrict__ count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_part) return;
-    double f;
-    const int ix = cic_node(pos[3 * (size_t)i], box, h, n, f);
-    const int iy = cic_node(pos[3 * (size_t)i + 1], box, h, n, f);
-    const int iz = cic_node(pos[3 * (size_t)i + 2], box, h, n, f);
-    const int k = (iz * n + iy) * n + ix;
-    key[i] = k;
-    rank[i] = atomicAdd(&count[k], 1);
+// Workgroups are dealt round-robin to the XCDs: the block's place when each
+// XCD is to take a contiguous eighth of the work (gridDim.x a multiple of
+// kXcds), so that neighbouring blocks' common data come from one L2.
+__device__ __forceinline__ int xcd_block() {
+    return (int)(blockIdx.x % kXcds) * (int)(gridDim.x / kXcds) + (int)(blockIdx.x / kXcds);
 }
 
+// Counting sort of the particles by bins of 8^3 lower CIC nodes (index (bz nb
+// + by) nb + bx): rank inside the bin, then a scatter to start[bin] + rank.
+// The sorted record holds the CIC fractions and mu, so the deposit and the
+// readout need neither the positions nor a division.  A bin's particles are
+// about one wave at mean density, and the phi values around it (13^3, 17 KB)
+// fit the L1, which is all the order that deposit and readout use; a sort by
+// single nodes needed a counter per node (for 2^21 particles on 256^3 nodes: an
+// atomic per particle on 67 MB of counters, clearing and scanning them, 0.26 ms
+// together; by bins, keys, scan and scatter take 0.11 ms).
+template <int PPT>
+__global__ __launch_bounds__(kKeysThreads) void k_pm_keys(const double *__restrict__ pos,
+                                                          int n_part, int n, double box, double h,
+                                                          int *__restrict__ key,
+                                                          int *__restrict__ rank,
+                                                          int *__restrict__ count) {
+    const int nb = n / kPmBin;
+    block_ranks<PPT>(n_part, key, rank, count, [&](size_t i) {
+        double f;
+        const int bx = cic_node(pos[3 * i], box, h, n, f) / kPmBin;
+        const int by = cic_node(pos[3 * i + 1], box, h, n, f) / kPmBin;
+        const int bz = cic_node(pos[3 * i + 2], box, h, n, f) / kPmBin;
+        return (bz * nb + by) * nb + bx;
+    });
+}
+
+// The deposit's blocks take the first kOverRun particles of a bin; the runs of
+// kOverRun after them are listed here.
+constexpr int kOverRun = 2048;
+
 // (Writing only the sorted index here and building the records in sorted
-// order with gathered reads took as long: 0.026 + 0.083 ms against 0.114.)
+// order with gathered reads took as long.)
 __global__ void k_pm_scatter(const double *__restrict__ pos, const double *__restrict__ mass,
                              const uint8_t *__restrict__ active, int n_part, int n, double box,
                              double h, const int *__restrict__ key, const int *__restrict__ rank,
-                             const int *__restrict__ start, double4 *__restrict__ rec,
-                             int *__restrict__ nkey, int *__restrict__ perm,
-                             uint8_t *__restrict__ recv) {
+                             const int *__restrict__ start, int *__restrict__ over,
+                             double4 *__restrict__ rec, int *__restrict__ nkey,
+                             int *__restrict__ perm) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_part) return;
-    const int k = key[i];
-    const int dst = start[k] + rank[i];
+    const int k = key[i], q = rank[i];
+    const int dst = start[k] + q;
+    if (q >= kOverRun && q % kOverRun == 0) {
+        const int at = atomicAdd(over, 1);
+        over[1 + 2 * at] = k;
+        over[2 + 2 * at] = dst;
+    }
     double4 r;
-    (void)cic_node(pos[3 * (size_t)i], box, h, n, r.x);
-    (void)cic_node(pos[3 * (size_t)i + 1], box, h, n, r.y);
-    (void)cic_node(pos[3 * (size_t)i + 2], box, h, n, r.z);
+    const int ix = cic_node(pos[3 * (size_t)i], box, h, n, r.x);
+    const int iy = cic_node(pos[3 * (size_t)i + 1], box, h, n, r.y);
+    const int iz = cic_node(pos[3 * (size_t)i + 2], box, h, n, r.z);
     r.w = mass ? mass[i] : 1.0;
     rec[dst] = r;
-    nkey[dst] = k;
-    perm[dst] = i;
-    recv[dst] = active ? (uint8_t)(active[i] != 0) : (uint8_t)1;
+    nkey[dst] = (iz * n + iy) * n + ix;
+    perm[dst] = active && !active[i] ? ~i : i;
 }
 
-// CIC deposit, split by how many particles a source node holds (a node's
-// particles are the sorted records start[k] .. start[k+1] - 1).
-//
-// Sparse source nodes (at most kDenseNode particles) are deposited brick by
-// brick: one block owns B^3 grid nodes (B = 16, or 8 on a 16^3 grid), lists
-// the particles of the sparse nodes among the (B+1)^3 source nodes that
-// reach them (offsets
-// 0 or -1 per axis), adds their weights into the brick in LDS and stores the
-// brick, so this part needs neither global atomics nor a cleared grid.  In
-// the uniform background most nodes hold 0 or 1 particle, where 8 global
-// atomics per particle dominated the deposit; a one-thread-per-node gather
-// cost as much (16 scattered start[] loads per node).
-//
-// Dense source nodes: the particles' 8 weights go through global atomics
-// after a segmented suffix sum over the wave (lanes that share a node hold
-// consecutive records; six shuffle steps leave each run's total with its
-// first lane, which alone issues the 8 FP64 atomics).  In halo cores this
-// replaces up to 64 serialised atomics on one address by one.  The bricks
-// run first; the atomics add on top of them.
-constexpr int kDenseNode = 8;
-
-// kBrick^3 nodes per block of kBrickThreads threads; kBrick <= n / 2 keeps the
-// (kBrick + 1) source nodes per axis distinct.
-template <int kBrick, int kBrickThreads>
-__global__ __launch_bounds__(kBrickThreads) void k_pm_deposit_brick(
-    const double4 *__restrict__ rec, const int *__restrict__ nkey, const int *__restrict__ start,
-    int n, int lg, double *__restrict__ rho) {
-    constexpr int kBrickSrc = (kBrick + 1) * (kBrick + 1) * (kBrick + 1);
-    constexpr int kBrickPer = (kBrickSrc + kBrickThreads - 1) / kBrickThreads;
+// CIC deposit.  One block owns B^3 grid nodes (B = 16, or 8 on a 16^3 grid)
+// and takes the particles of the bins that reach them: its own and the next
+// lower ones, (B / 8 + 1)^3 in all.  Each adds those of its 8 weights that
+// fall into the brick in LDS, and the brick is stored, so this needs neither
+// global atomics nor a cleared grid.  Every bin is read by up to 8 bricks
+// (3.4 on average); the reads come from the caches.  2^21 clustered particles
+// on 256^3 nodes: 0.089 ms, and 0.009 for the runs of dense bins below (0.117
+// and 0.015 when single nodes were sorted and looked up here).
+template <int kBrick>
+__global__ __launch_bounds__(512) void k_pm_deposit_brick(const double4 *__restrict__ rec,
+                                                          const int *__restrict__ nkey,
+                                                          const int *__restrict__ start, int n,
+                                                          int lg, double *__restrict__ rho) {
+    constexpr int kThreads = 512;
+    constexpr int kSide = kBrick / kPmBin + 1;
+    constexpr int kBins = kSide * kSide * kSide;
     __shared__ double acc[kBrick * kBrick * kBrick];
-    __shared__ int src_a[kBrickSrc];          // first record of each listed source node
-    __shared__ int pre[kBrickSrc + 1];        // exclusive prefix of their sparse counts
-    __shared__ int wsum[kBrickThreads / kWave];
+    __shared__ int first[kBins], pre[kBins + 1];
     const int t = threadIdx.x;
-    const int lane = t & (kWave - 1), wave = t / kWave;
-    const int msk = n - 1;
+    const int msk = n - 1, nb8 = n / kPmBin;
     const int nb = n / kBrick;
-    const int b = blockIdx.x;
+    const int b = xcd_block();
     const int x0 = (b % nb) * kBrick, y0 = ((b / nb) % nb) * kBrick, z0 = (b / (nb * nb)) * kBrick;
-    for (int j = t; j < kBrick * kBrick * kBrick; j += kBrickThreads) acc[j] = 0.0;
-    // source node j = (sz * 9 + sy) * 9 + sx covers (x0 - 1 + sx, y0 - 1 + sy, z0 - 1 + sz)
-    int len[kBrickPer];
-    int mine = 0;
-#pragma unroll
-    for (int q = 0; q < kBrickPer; ++q) {
-        const int j = t * kBrickPer + q;
-        len[q] = 0;
-        if (j < kBrickSrc) {
-            const int sx = j % (kBrick + 1), sy = (j / (kBrick + 1)) % (kBrick + 1),
-                      sz = j / ((kBrick + 1) * (kBrick + 1));
-            const size_t g = ((size_t)((z0 - 1 + sz) & msk) * n + ((y0 - 1 + sy) & msk)) * n +
-                             ((x0 - 1 + sx) & msk);
-            const int a0 = start[g], a1 = start[g + 1];
-            src_a[j] = a0;
-            len[q] = a1 - a0 <= kDenseNode ? a1 - a0 : 0;
+    for (int j = t; j < kBrick * kBrick * kBrick; j += kThreads) acc[j] = 0.0;
+    if (t < kWave) {
+        int len = 0;
+        if (t < kBins) {
+            const int bx = (x0 / kPmBin - 1 + t % kSide) & (nb8 - 1);
+            const int by = (y0 / kPmBin - 1 + (t / kSide) % kSide) & (nb8 - 1);
+            const int bz = (z0 / kPmBin - 1 + t / (kSide * kSide)) & (nb8 - 1);
+            const int c = (bz * nb8 + by) * nb8 + bx;
+            first[t] = start[c];
+            len = min(start[c + 1] - start[c], kOverRun);
         }
-        mine += len[q];
+        int incl = len;
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int y = __shfl_up(incl, off, kWave);
+            if (t >= off) incl += y;
+        }
+        if (t < kBins) pre[t + 1] = incl;
+        if (t == 0) pre[0] = 0;
     }
-    // block exclusive scan of the per-thread totals
-    int incl = mine;
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int y = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += y;
-    }
-    if (lane == kWave - 1) wsum[wave] = incl;
     __syncthreads();
-    int base = incl - mine, total = 0;
-    for (int w = 0; w < kBrickThreads / kWave; ++w) {
-        if (w < wave) base += wsum[w];
-        total += wsum[w];
-    }
-#pragma unroll
-    for (int q = 0; q < kBrickPer; ++q) {
-        const int j = t * kBrickPer + q;
-        if (j < kBrickSrc) pre[j] = base;
-        base += len[q];
-    }
-    if (t == 0) pre[kBrickSrc] = total;
-    __syncthreads();
-    for (int i = t; i < total; i += kBrickThreads) {
-        // the listed node holding entry i: the last j with pre[j] <= i
-        int lo = 0, hi = kBrickSrc;   // pre[lo] <= i < pre[hi]
+    const int total = pre[kBins];
+    for (int i = t; i < total; i += kThreads) {
+        // the bin holding entry i: the last j with pre[j] <= i
+        int lo = 0, hi = kBins;
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (pre[mid] <= i) lo = mid;
             else hi = mid;
         }
-        const int q = src_a[lo] + (i - pre[lo]);
-        const double4 r = rec[q];
+        const int q = first[lo] + (i - pre[lo]);
         const int k = nkey[q];
-        const int x = k & msk, y = (k >> lg) & msk, z = k >> (2 * lg);
+        const double4 r = rec[q];   // loaded beside the key, not after it
+        // the lower node relative to the brick, -1 .. kBrick - 1 where it reaches it
+        const int x = (((k & msk) - x0 + 1) & msk) - 1;
+        const int y = ((((k >> lg) & msk) - y0 + 1) & msk) - 1;
+        const int z = (((k >> (2 * lg)) - z0 + 1) & msk) - 1;
+        if (x >= kBrick || y >= kBrick || z >= kBrick) continue;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const int cx = (c >> 2) & 1, cy = (c >> 1) & 1, cz = c & 1;
-            const int tx = (x + cx - x0) & msk, ty = (y + cy - y0) & msk, tz = (z + cz - z0) & msk;
-            if (tx < kBrick && ty < kBrick && tz < kBrick) {
-                const double wx = cx ? r.x : 1.0 - r.x;
-                const double wy = cy ? r.y : 1.0 - r.y;
-                const double wz = cz ? r.z : 1.0 - r.z;
+            const int tx = x + ((c >> 2) & 1), ty = y + ((c >> 1) & 1), tz = z + (c & 1);
+            if ((unsigned)tx < kBrick && (unsigned)ty < kBrick && (unsigned)tz < kBrick) {
+                const double wx = (c & 4) ? r.x : 1.0 - r.x;
+                const double wy = (c & 2) ? r.y : 1.0 - r.y;
+                const double wz = (c & 1) ? r.z : 1.0 - r.z;
                 atomicAdd(&acc[(tz * kBrick + ty) * kBrick + tx], r.w * wx * wy * wz);
             }
         }
     }
     __syncthreads();
-    for (int j = t; j < kBrick * kBrick * kBrick; j += kBrickThreads) {
+    for (int j = t; j < kBrick * kBrick * kBrick; j += kThreads) {
         const int tx = j % kBrick, ty = (j / kBrick) % kBrick, tz = j / (kBrick * kBrick);
         rho[((size_t)(z0 + tz) * n + (y0 + ty)) * n + (x0 + tx)] = acc[j];
     }
 }
 
-__global__ __launch_bounds__(256) void k_pm_deposit(const double4 *__restrict__ rec,
-                                                    const int *__restrict__ nkey,
-                                                    const int *__restrict__ start, int n_part,
-                                                    double *__restrict__ rho, int n) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & (kWave - 1);
-    int key = -1 - lane;   // idle and sparse lanes: keys no other lane holds
-    bool dense = false;
-    double v[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = 0.0;
-    if (p < n_part) {
-        const int k = nkey[p];
-        dense = start[k + 1] - start[k] > kDenseNode;
-        if (dense) {
-            const double4 r = rec[p];
-            key = k;
+// The listed runs of dense bins, one block each: their weights are added in
+// LDS on the (8 + 1)^3 nodes that a bin reaches, and those sums on top of the
+// bricks with one global atomic per node.
+__global__ __launch_bounds__(256) void k_pm_deposit_over(const double4 *__restrict__ rec,
+                                                         const int *__restrict__ nkey,
+                                                         const int *__restrict__ start,
+                                                         const int *__restrict__ over, int n,
+                                                         int lg, double *__restrict__ rho) {
+    constexpr int S = kPmBin + 1;
+    __shared__ double acc[S * S * S];
+    const int msk = n - 1, nb = n / kPmBin;
+    const int runs = over[0];
+    for (int e = blockIdx.x; e < runs; e += gridDim.x) {
+        const int bin = over[1 + 2 * e], q0 = over[2 + 2 * e];
+        const int q1 = min(q0 + kOverRun, start[bin + 1]);
+        const int x0 = (bin % nb) * kPmBin, y0 = ((bin / nb) % nb) * kPmBin,
+                  z0 = (bin / (nb * nb)) * kPmBin;
+        for (int j = threadIdx.x; j < S * S * S; j += blockDim.x) acc[j] = 0.0;
+        __syncthreads();
+        for (int q = q0 + threadIdx.x; q < q1; q += blockDim.x) {
+            const int k = nkey[q];
+            const int x = (k & msk) - x0, y = ((k >> lg) & msk) - y0, z = (k >> (2 * lg)) - z0;
+            const double4 r = rec[q];
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const double wx = (c & 4) ? r.x : 1.0 - r.x;
                 const double wy = (c & 2) ? r.y : 1.0 - r.y;
                 const double wz = (c & 1) ? r.z : 1.0 - r.z;
-                v[c] = r.w * wx * wy * wz;
+                atomicAdd(&acc[((z + (c & 1)) * S + y + ((c >> 1) & 1)) * S + x + ((c >> 2) & 1)],
+                          r.w * wx * wy * wz);
             }
         }
-    }
-    // no dense particle in this wave: nothing to add
-    if (!__ballot(dense)) return;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int k2 = __shfl_down(key, off, kWave);
-        const bool same = lane + off < kWave && k2 == key;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const double o = __shfl_down(v[c], off, kWave);
-            if (same) v[c] += o;
+        __syncthreads();
+        for (int j = threadIdx.x; j < S * S * S; j += blockDim.x) {
+            const size_t x = (x0 + j % S) & msk, y = (y0 + (j / S) % S) & msk,
+                         z = (z0 + j / (S * S)) & msk;
+            if (acc[j] != 0.0) atomicAdd(rho + (z * n + y) * n + x, acc[j]);
         }
-    }
-    const int prev = __shfl_up(key, 1, kWave);
-    if (!dense || (lane > 0 && prev == key)) return;
-    const int m = n - 1;
-    const int ix = key & m, iy = (key / n) & m, iz = key / (n * n);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const size_t x = (ix + ((c >> 2) & 1)) & m;
-        const size_t y = (iy + ((c >> 1) & 1)) & m;
-        const size_t z = (iz + (c & 1)) & m;
-        atomicAdd(rho + (z * n + y) * n + x, v[c]);
+        __syncthreads();
     }
 }
 
-// Twiddles tw[m] = exp(-2 pi i m / n), m < n/2, and the kernel tables.
-__global__ void k_pm_tables(int n, double box, double x_s, double2 *tw, double *w1,
-                            double *k2) {
+// Twiddles tw[m] = exp(-2 pi i m / n), m < n/2, the kernel tables, and the
+// sort array cleared (16-byte stores; its length is a multiple of 4 ints).
+__global__ void k_pm_prepare(int n, double box, double x_s, double2 *tw, double *w1, double *k2,
+                             int4 *zero, size_t n4) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t j = i; j < n4; j += (size_t)gridDim.x * blockDim.x) zero[j] = make_int4(0, 0, 0, 0);
     if (i < n / 2) {
         double s, c;
         sincospi(2.0 * (double)i / (double)n, &s, &c);
@@ -518,65 +499,91 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_strided(double2 *__restrict
     }
 }
 
-// Readout: per receiver, the 4-point difference of phi along each axis at
-// the 8 CIC nodes and their CIC-weighted sum.  Along x the six values
-// phi[i0-2 .. i0+3] of each (y, z) node pair give D4 at i0 and i0 + 1; the
-// same for y and z.
-__device__ __forceinline__ double d4_at(const double *v) {
-    // v[0..4] = phi[m-2 .. m+2]
-    return (v[0] - 8.0 * v[1] + 8.0 * v[3] - v[4]) / 12.0;
+// Readout: per receiver, the 4-point difference of phi along each axis at the
+// 8 CIC nodes and their CIC-weighted sum.  The stencil is the four x rows of
+// the node pairs in y and z (six values each: D4 at both x nodes), and for the
+// differences along y and z the two x nodes of the 16 rows at distance 1 and 2
+// from them, interpolated along x first: 28 pairs of x neighbours.
+//
+// The kernel is bound by its gathers: each lane's row is a cache line of its
+// own, and the address unit takes a lane per cycle whatever the load's width
+// (64 accesses per load and wave by its counters).  So the pairs are loaded 16
+// bytes at a time, 28 loads instead of 72: 2^21 particles on 256^3 nodes 0.219
+// -> 0.182 ms, 262144 on 128^3 0.031 -> 0.022 ms, although the particles are no
+// longer sorted by node, which let some of the 72 share lines.  (Staging phi
+// per 16^3-node brick in LDS and reading the stencils from there took 0.222 ms,
+// 0.106 of it for the staging alone.)
+__device__ __forceinline__ double d4_of(double a, double b, double c, double d) {
+    return (a - 8.0 * b + 8.0 * c - d) / 12.0;   // phi[m-2], [m-1], [m+1], [m+2]
 }
 
-// (Staging phi per brick in LDS and reading the stencils from there was
-// slower: 241 us with 16^3 bricks and 275 us with 8^3 against 216 us for
-// this per-particle gather on clustered128's 256^3 grid.)
-__global__ void k_pm_readout(const double4 *__restrict__ rec, const int *__restrict__ nkey,
-                             const int *__restrict__ perm, const uint8_t *__restrict__ recv,
-                             int n_part, const double *__restrict__ phi, int n,
-                             double *__restrict__ acc) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_part) return;
-    const size_t i = (size_t)perm[p];
-    if (!recv[p]) {
-        acc[3 * i] = 0.0;
-        acc[3 * i + 1] = 0.0;
-        acc[3 * i + 2] = 0.0;
-        return;
-    }
-    const double4 r = rec[p];
-    const int key = nkey[p];
-    const int m = n - 1;
-    const int i0[3] = {key & m, (key / n) & m, key / (n * n)};
-    const double f[3] = {r.x, r.y, r.z};
-    const size_t str[3] = {1, (size_t)n, (size_t)n * n};
-    double out[3];
+// Two values on any 8-byte boundary, as one 16-byte load.
+typedef double Pair8 __attribute__((ext_vector_type(2), aligned(8)));
+
+__global__ __launch_bounds__(256) void k_pm_readout(const double4 *__restrict__ rec,
+                                                    const int *__restrict__ nkey,
+                                                    const int *__restrict__ perm, int n_part,
+                                                    const double *__restrict__ phi, int n, int lg,
+                                                    double *__restrict__ acc) {
+    const long long at = (long long)xcd_block() * blockDim.x + threadIdx.x;
+    if (at >= n_part) return;
+    const int p = (int)at;
+    const int who = perm[p];
+    double ox = 0.0, oy = 0.0, oz = 0.0;
+    if (who >= 0) {
+        const double4 r = rec[p];
+        const int key = nkey[p];
+        const int m = n - 1;
+        const int ix = key & m, iy = (key >> lg) & m, iz = key >> (2 * lg);
+        // values x, x + 1 of a row (x already wrapped): the pair past the
+        // row's end wraps to its start
+        auto pair = [&](const double *row, int x) {
+            if (x == m) return make_double2(row[m], row[0]);
+            const Pair8 v = *reinterpret_cast<const Pair8 *>(row + x);
+            return make_double2(v.x, v.y);
+        };
+        const double gx = 1.0 - r.x, gy = 1.0 - r.y, gz = 1.0 - r.z;
+        const int xm = (ix - 2) & m, xp = (ix + 2) & m;
+        size_t ry[6], rz[6];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        // the two axes other than d
-        const int a = d == 0 ? 1 : 0;
-        const int b = d == 2 ? 1 : 2;
-        double sum = 0.0;
+        for (int s = 0; s < 6; ++s) {
+            ry[s] = (size_t)((iy - 2 + s) & m) * n;
+            rz[s] = (size_t)((iz - 2 + s) & m) * n * n;
+        }
+        double c[2][2];   // x-interpolated values of the central rows
 #pragma unroll
-        for (int ca = 0; ca < 2; ++ca) {
-            const double wa = ca ? f[a] : 1.0 - f[a];
-            const size_t oa = (size_t)((i0[a] + ca) & m) * str[a];
+        for (int a = 0; a < 2; ++a) {
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const double wb = cb ? f[b] : 1.0 - f[b];
-                const size_t ob = (size_t)((i0[b] + cb) & m) * str[b];
-                double v[6];
-#pragma unroll
-                for (int s = 0; s < 6; ++s)
-                    v[s] = phi[oa + ob + (size_t)((i0[d] - 2 + s + n) & m) * str[d]];
-                const double line = (1.0 - f[d]) * d4_at(v) + f[d] * d4_at(v + 1);
-                sum += wa * wb * line;
+            for (int b = 0; b < 2; ++b) {
+                const double *row = phi + ry[2 + a] + rz[2 + b];
+                const double2 l = pair(row, xm), q = pair(row, ix), h = pair(row, xp);
+                const double line = gx * d4_of(l.x, l.y, q.y, h.x) + r.x * d4_of(l.y, q.x, h.x, h.y);
+                ox += (a ? r.y : gy) * (b ? r.z : gz) * line;
+                c[a][b] = gx * q.x + r.x * q.y;
             }
         }
-        out[d] = sum;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            double y[4], z[4];   // rows -2, -1, +2, +3 along y (at node b of z), along z (at b of y)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int o = s < 2 ? s : s + 2;
+                const double2 u = pair(phi + ry[o] + rz[2 + b], ix);
+                const double2 v = pair(phi + ry[2 + b] + rz[o], ix);
+                y[s] = gx * u.x + r.x * u.y;
+                z[s] = gx * v.x + r.x * v.y;
+            }
+            oy += (b ? r.z : gz) * (gy * d4_of(y[0], y[1], c[1][b], y[2]) +
+                                    r.y * d4_of(y[1], c[0][b], y[2], y[3]));
+            oz += (b ? r.y : gy) * (gz * d4_of(z[0], z[1], c[b][1], z[2]) +
+                                    r.z * d4_of(z[1], c[b][0], z[2], z[3]));
+        }
     }
-    acc[3 * i] = out[0];
-    acc[3 * i + 1] = out[1];
-    acc[3 * i + 2] = out[2];
+    // who < 0: ~particle, which receives nothing
+    const size_t i = (size_t)(who >= 0 ? who : ~who);
+    acc[3 * i] = ox;
+    acc[3 * i + 1] = oy;
+    acc[3 * i + 2] = oz;
 }
 
 template <int N>
@@ -605,49 +612,74 @@ hipError_t launch_fft_chain_n(const PmArgs &a, hipStream_t s, hipEvent_t *ev) {
 
 }  // namespace
 
-hipError_t launch_pm_tables(int n, double box, double x_s, double2 *tw, double *w1, double *k2,
-                            hipStream_t s) {
-    k_pm_tables<<<(n + 255) / 256, 256, 0, s>>>(n, box, x_s, tw, w1, k2);
+PmSort pm_sort_layout(int *bins, int n, int n_part) {
+    const size_t nb = (size_t)n / kPmBin, cells = nb * nb * nb;
+    auto even = [](size_t v) { return (v + 3) & ~(size_t)3; };
+    PmSort p{};
+    size_t at = 0;
+    p.start = bins;
+    at += even(cells + 1);
+    p.over = bins + at;
+    at += even(1 + 2 * ((size_t)n_part / kOverRun + 1));
+    p.status = (unsigned long long *)(bins + at);
+    at += even(2 * scan1_status_needed(cells));
+    p.stall = (unsigned long long *)(bins + at);
+    p.ctr = bins + at + 2;
+    p.ints = at + 4;
+    return p;
+}
+
+hipError_t launch_pm_prepare(int n, double box, double x_s, double2 *tw, double *w1, double *k2,
+                             const PmSort &ps, hipStream_t s) {
+    const size_t n4 = ps.ints / 4;
+    const size_t blocks = (n4 + 1023) / 1024;
+    const unsigned grid = (unsigned)(blocks < (size_t)n / 256 + 1 ? n / 256 + 1
+                                     : blocks > 4096              ? 4096
+                                                                  : blocks);
+    k_pm_prepare<<<grid, 256, 0, s>>>(n, box, x_s, tw, w1, k2, (int4 *)ps.start, n4);
     return hipGetLastError();
 }
 
 hipError_t launch_pm_sort(const double *pos, const double *mass, const uint8_t *active,
                           int n_part, int n, double box, double h, int *key, int *rank,
-                          int *count, int *bsum, double4 *rec, int *nkey, int *perm,
-                          uint8_t *recv, hipStream_t s) {
-    const size_t cells = (size_t)n * n * n;
-    hipError_t e;
-    if ((e = launch_fill_i32(count, 0, cells + 1, s)) != hipSuccess) return e;
-    const unsigned grid = (unsigned)((n_part + 255) / 256);
-    if (n_part > 0) {
-        k_pm_keys<<<grid, 256, 0, s>>>(pos, n_part, n, box, h, key, rank, count);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+                          const PmSort &ps, int *bsum, double4 *rec, int *nkey, int *perm,
+                          hipStream_t s) {
     if (n_part == 0) return hipSuccess;
-    // start[k] = first sorted index of node k
-    if ((e = launch_scan(count, count, cells, bsum, s)) != hipSuccess) return e;
-    k_pm_scatter<<<grid, 256, 0, s>>>(pos, mass, active, n_part, n, box, h, key, rank, count, rec,
-                                      nkey, perm, recv);
+    const size_t nb = (size_t)n / kPmBin, cells = nb * nb * nb;
+    const int ppt = keys_per_thread(n_part);
+    auto fn = ppt == 8   ? k_pm_keys<8>
+              : ppt == 4 ? k_pm_keys<4>
+              : ppt == 2 ? k_pm_keys<2>
+                         : k_pm_keys<1>;
+    const int per = kKeysThreads * ppt;
+    fn<<<(unsigned)((n_part + per - 1) / per), kKeysThreads, 0, s>>>(pos, n_part, n, box, h, key,
+                                                                     rank, ps.start);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // start[k] = first sorted index of bin k
+    if ((e = launch_scan1(ps.start, ps.start, cells, ps.status, ps.ctr, ps.stall, bsum, s)) !=
+        hipSuccess)
+        return e;
+    k_pm_scatter<<<(unsigned)((n_part + 255) / 256), 256, 0, s>>>(
+        pos, mass, active, n_part, n, box, h, key, rank, ps.start, ps.over, rec, nkey, perm);
     return hipGetLastError();
 }
 
-hipError_t launch_pm_deposit(const double4 *rec, const int *nkey, const int *start, int n_part,
+hipError_t launch_pm_deposit(const double4 *rec, const int *nkey, const PmSort &ps, int n_part,
                              double *rho, int n, hipStream_t s) {
-    int lg = 0;
-    while ((1 << lg) < n) ++lg;
+    const int lg = __builtin_ctz((unsigned)n);
     if (n >= 32) {
-        const size_t nb = (size_t)n / 16;
-        k_pm_deposit_brick<16, 1024><<<(unsigned)(nb * nb * nb), 1024, 0, s>>>(rec, nkey, start,
-                                                                              n, lg, rho);
+        const unsigned nb = (unsigned)n / 16;
+        k_pm_deposit_brick<16><<<nb * nb * nb, 512, 0, s>>>(rec, nkey, ps.start, n, lg, rho);
     } else {
-        const size_t nb = (size_t)n / 8;
-        k_pm_deposit_brick<8, 256><<<(unsigned)(nb * nb * nb), 256, 0, s>>>(rec, nkey, start, n,
-                                                                           lg, rho);
+        const unsigned nb = (unsigned)n / 8;
+        k_pm_deposit_brick<8><<<nb * nb * nb, 512, 0, s>>>(rec, nkey, ps.start, n, lg, rho);
     }
-    hipError_t e;
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (n_part == 0) return hipSuccess;
-    k_pm_deposit<<<(unsigned)((n_part + 255) / 256), 256, 0, s>>>(rec, nkey, start, n_part, rho, n);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || n_part <= kOverRun) return e;
+    const int runs = n_part / kOverRun;
+    k_pm_deposit_over<<<(unsigned)(runs < 1024 ? runs : 1024), 256, 0, s>>>(rec, nkey, ps.start,
+                                                                          ps.over, n, lg, rho);
     return hipGetLastError();
 }
 
@@ -664,12 +696,12 @@ hipError_t launch_pm_fft_chain(const PmArgs &a, hipStream_t s, hipEvent_t *ev) {
     }
 }
 
-hipError_t launch_pm_readout(const double4 *rec, const int *nkey, const int *perm,
-                             const uint8_t *recv, int n_part, const double *phi, int n,
-                             double *acc, hipStream_t s) {
+hipError_t launch_pm_readout(const double4 *rec, const int *nkey, const int *perm, int n_part,
+                             const double *phi, int n, double *acc, hipStream_t s) {
     if (n_part == 0) return hipSuccess;
-    k_pm_readout<<<(unsigned)((n_part + 255) / 256), 256, 0, s>>>(rec, nkey, perm, recv, n_part,
-                                                                 phi, n, acc);
+    const unsigned per_xcd = (unsigned)((n_part + 256 * kXcds - 1) / (256 * kXcds));
+    k_pm_readout<<<per_xcd * kXcds, 256, 0, s>>>(rec, nkey, perm, n_part, phi, n,
+                                                 __builtin_ctz((unsigned)n), acc);
     return hipGetLastError();
 }
 
