@@ -1723,11 +1723,15 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
     if ((rc = ensure(h, h->kdk_tq, np1 * sizeof(int), s))) return rc;
     if ((rc = ensure(h, h->kdk_tnext, np1 * sizeof(int), s))) return rc;
     if ((rc = ensure(h, h->kdk_due, np1, s))) return rc;
-    if ((rc = ensure(h, h->kdk_scal, 8 * sizeof(int), s))) return rc;
+    // [0 .. 8] the rung census, [10 .. 11] pairs, then the particles due at
+    // each of the at most 64 * 128 sub-steps
+    constexpr int kCounts = 12;
+    const size_t scal_ints = kCounts + (size_t)n_steps * (1u << max_rung);
+    if ((rc = ensure(h, h->kdk_scal, scal_ints * sizeof(int), s))) return rc;
     double *acc = (double *)h->kdk_acc.p, *acc_lr = (double *)h->kdk_lr.p;
     int *t_q = (int *)h->kdk_tq.p, *t_next = (int *)h->kdk_tnext.p;
-    int *scal = (int *)h->kdk_scal.p;   // [0] highest rung, [1] due count, [2..3] pairs
-    unsigned long long *pairs = (unsigned long long *)(scal + 2);
+    int *scal = (int *)h->kdk_scal.p;
+    unsigned long long *pairs = (unsigned long long *)(scal + 10);
     uint8_t *due = (uint8_t *)h->kdk_due.p;
 
     // the call's softening is eps for both the forces and eq. rung
@@ -1760,7 +1764,7 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
     int sr_calls = 0, lr_calls = 0;
     // short-range accelerations at the synchronised start: they set the rungs
     // (eq. rung, no momentum update) and drive the half kicks
-    P3M_HIP(launch_fill_i32(scal, 0, 8, s));
+    P3M_HIP(launch_fill_i32(scal, 0, scal_ints, s));
     if ((rc = run(h, r, h->work))) return rc;
     ++sr_calls;
     if (np > 0) P3M_HIP(launch_kdk_accum(h->last_counters, pairs, s));
@@ -1770,9 +1774,10 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
     k.max_rung = max_rung;
     k.fixed = fixed ? 1 : 0;
     P3M_HIP(launch_kdk_assign(acc, np, k, rung, scal, s));
-    int L = 0;
-    P3M_HIP(hipMemcpyAsync(&L, scal, sizeof(int), hipMemcpyDeviceToHost, s));
+    int census[9];
+    P3M_HIP(hipMemcpyAsync(census, scal, sizeof(census), hipMemcpyDeviceToHost, s));
     P3M_HIP(hipStreamSynchronize(s));
+    const int L = census[8];
     if (L > max_rung)
         return set_error(P3M_EINVAL, "input rung %d exceeds max_rung %d", L, max_rung);
     k.L = L;
@@ -1789,29 +1794,44 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
         P3M_HIP(launch_axpy3(vel, acc_lr, np, (double)(target - t_lr) * k.half_tau, s));
         t_lr = target;
     }
+    // Every sub-step has due particles unless rung L has emptied by down-jumps.
+    // With a wave's worth of particles on it (or fixed rungs, which keep
+    // theirs) the sub-steps are queued without asking: a wait per sub-step
+    // leaves the GPU idle for 45 to 60 us, and a force call without receivers,
+    // should one occur, costs no more than the drift and the wait did.
+    const bool ask = !fixed && census[L] < kWave;
+    const int substeps = k.period / 2;
+    KdkAdvance adv{pos, vel, acc, due, rung, t_q, t_next, np, tau, box, h->last_counters, pairs};
+    P3M_HIP(launch_kdk_advance(adv, false, true, 0, k, scal + kCounts, s));
     for (int t = 2; t <= k.period; t += 2) {
-        P3M_HIP(launch_kdk_drift(pos, vel, np, tau, box, s));
-        P3M_HIP(launch_fill_i32(scal + 1, 0, 1, s));
-        P3M_HIP(launch_kdk_due(t_next, np, t, due, scal + 1, s));
-        int n_due = 0;
-        P3M_HIP(hipMemcpyAsync(&n_due, scal + 1, sizeof(int), hipMemcpyDeviceToHost, s));
-        P3M_HIP(hipStreamSynchronize(s));
+        int n_due = 1;
+        if (ask) {
+            P3M_HIP(hipMemcpyAsync(&n_due, scal + kCounts + t / 2 - 1, sizeof(int),
+                                   hipMemcpyDeviceToHost, s));
+            P3M_HIP(hipStreamSynchronize(s));
+        }
         if (n_due > 0) {
             r.sel = due;
             r.sel_kind = SEL_MASK;
             if ((rc = run(h, r, h->work))) return rc;
-            ++sr_calls;
-            P3M_HIP(launch_kdk_accum(h->last_counters, pairs, s));
-            P3M_HIP(launch_kdk_kick(vel, acc, due, np, t, k, rung, t_q, t_next, s));
+            adv.counters = h->last_counters;
         }
-        if (n_grid && t % span0 == 0) {
+        const bool last = t == k.period, lr = n_grid && t % span0 == 0;
+        int *next_due = scal + kCounts + t / 2;
+        // the long-range kick comes between the kick and the drift
+        if (n_due > 0)
+            P3M_HIP(launch_kdk_advance(adv, true, !last && !lr, t, k, last ? nullptr : next_due, s));
+        if (lr) {
             if ((rc = lr_run(h, pos, mass, nullptr, np, box, n_grid, x_s, acc_lr, s))) return rc;
             ++lr_calls;
-            const int target = t == k.period ? k.period : t + span0 / 2;
+            const int target = last ? k.period : t + span0 / 2;
             P3M_HIP(launch_axpy3(vel, acc_lr, np, (double)(target - t_lr) * k.half_tau, s));
             t_lr = target;
         }
+        if (!last && (lr || n_due == 0))
+            P3M_HIP(launch_kdk_advance(adv, false, true, t, k, next_due, s));
     }
+    int counts[64 << 7];
     h->kdk_stats = p3m_kdk_stats{};
     h->kdk_stats.n = n;
     h->kdk_stats.highest_rung = L;
@@ -1821,7 +1841,12 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
     h->kdk_stats.ms_total = -1.0f;
     unsigned long long total = 0;
     P3M_HIP(hipMemcpyAsync(&total, pairs, sizeof(total), hipMemcpyDeviceToHost, s));
+    P3M_HIP(hipMemcpyAsync(counts, scal + kCounts, (size_t)substeps * sizeof(int),
+                           hipMemcpyDeviceToHost, s));
     P3M_HIP(hipStreamSynchronize(s));
+    // the sub-steps that kicked
+    sr_calls += (int)std::count_if(counts, counts + substeps, [](int c) { return c > 0; });
+    h->kdk_stats.sr_calls = sr_calls;
     h->kdk_stats.interactions = (int64_t)total;
     if (e0) {
         P3M_HIP(hipEventRecord(e1, s));

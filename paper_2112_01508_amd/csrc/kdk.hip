@@ -33,18 +33,29 @@ __device__ __forceinline__ int rung_of(double ax, double ay, double az, const Kd
 
 __device__ __forceinline__ int span_of(int l, int L) { return 1 << (L + 1 - l); }
 
+// census: [0 .. 7] particles per rung, [8] the highest rung.  Counted per
+// block first: one device atomic per particle on the same address took 25 us
+// for 110592 particles.
 __global__ void k_kdk_assign(const double *__restrict__ acc, int n, KdkArgs k,
-                             uint8_t *__restrict__ rung, int *__restrict__ max_rung) {
+                             uint8_t *__restrict__ rung, int *__restrict__ census) {
+    __shared__ int cnt[9];
+    if (threadIdx.x < 9) cnt[threadIdx.x] = 0;
+    __syncthreads();
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int l;
-    if (k.fixed) {
-        l = rung[i];
-    } else {
-        l = rung_of(acc[3 * (size_t)i], acc[3 * (size_t)i + 1], acc[3 * (size_t)i + 2], k);
-        rung[i] = (uint8_t)l;
+    if (i < n) {
+        int l;
+        if (k.fixed) {
+            l = rung[i];
+        } else {
+            l = rung_of(acc[3 * (size_t)i], acc[3 * (size_t)i + 1], acc[3 * (size_t)i + 2], k);
+            rung[i] = (uint8_t)l;
+        }
+        if (l < 8) atomicAdd(&cnt[l], 1);
+        atomicMax(&cnt[8], l);
     }
-    atomicMax(max_rung, l);
+    __syncthreads();
+    if (threadIdx.x < 8 && cnt[threadIdx.x]) atomicAdd(&census[threadIdx.x], cnt[threadIdx.x]);
+    if (threadIdx.x == 8) atomicMax(&census[8], cnt[8]);
 }
 
 // The half kicks from the synchronised start.
@@ -61,43 +72,18 @@ __global__ void k_kdk_first(double *__restrict__ vel, const double *__restrict__
     t_next[i] = sp;
 }
 
-__global__ void k_kdk_drift(double *__restrict__ pos, const double *__restrict__ vel, size_t n3,
-                            double tau, double box) {
-    const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n3) return;
-    double x = pos[j] + vel[j] * tau;
-    double r = fmod(x, box);
-    if (r < 0.0) r += box;
-    if (r >= box) r -= box;
-    pos[j] = r;
-}
-
-__global__ void k_kdk_due(const int *__restrict__ t_next, int n, int t, uint8_t *__restrict__ due,
-                          int *__restrict__ n_due) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const bool d = t_next[i] == t;
-    due[i] = (uint8_t)d;
-    // one atomic per wave
-    const unsigned long long b = __ballot(d);
-    if (b && (threadIdx.x & (kWave - 1)) == (unsigned)(__ffsll((long long)b) - 1))
-        atomicAdd(n_due, __popcll(b));
-}
-
-__global__ void k_kdk_kick(double *__restrict__ vel, const double *__restrict__ acc,
-                           const uint8_t *__restrict__ due, int n, int t, KdkArgs k,
-                           uint8_t *__restrict__ rung, int *__restrict__ t_q,
-                           int *__restrict__ t_next) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || !due[i]) return;
-    const double ax = acc[3 * (size_t)i], ay = acc[3 * (size_t)i + 1], az = acc[3 * (size_t)i + 2];
+// The kick of a due particle at time t (v += a dk) and its rung's update.
+__device__ __forceinline__ void kick(double (&v)[3], const double *__restrict__ a, int i, int t,
+                                     const KdkArgs &k, uint8_t *__restrict__ rung,
+                                     int *__restrict__ t_q, int *__restrict__ t_next) {
+    const double ax = a[3 * (size_t)i], ay = a[3 * (size_t)i + 1], az = a[3 * (size_t)i + 2];
     int l = rung[i];
     const bool last = t == k.period;
     const int target = last ? k.period : t + span_of(l, k.L) / 2;
     const double dk = (double)(target - t_q[i]) * k.half_tau;
-    vel[3 * (size_t)i] = vel[3 * (size_t)i] + ax * dk;
-    vel[3 * (size_t)i + 1] = vel[3 * (size_t)i + 1] + ay * dk;
-    vel[3 * (size_t)i + 2] = vel[3 * (size_t)i + 2] + az * dk;
+    v[0] = v[0] + ax * dk;
+    v[1] = v[1] + ay * dk;
+    v[2] = v[2] + az * dk;
     t_q[i] = target;
     if (k.fixed) {
         if (!last) t_next[i] = t + span_of(l, k.L);
@@ -119,6 +105,59 @@ __global__ void k_kdk_kick(double *__restrict__ vel, const double *__restrict__ 
     t_next[i] = (t / sp + 1) * sp;
 }
 
+// What happens to a particle between two force calls: its kick at time t if it
+// is due (KICK), then the drift over tau and whether it is due at t + 2 (DRIFT;
+// the due particles counted per block).  The first thread adds the force
+// call's accepted pairs to the period's total.  (As kernels of their own with
+// one atomic per wave on the count these took 37 us per sub-step of 110592
+// particles, 22 of them in the counting; 7 us together.)
+template <bool KICK, bool DRIFT>
+__global__ void k_kdk_advance(double *__restrict__ pos, double *__restrict__ vel,
+                              const double *__restrict__ acc, uint8_t *__restrict__ due, int n,
+                              int t, KdkArgs k, double tau, double box,
+                              uint8_t *__restrict__ rung, int *__restrict__ t_q,
+                              int *__restrict__ t_next, int *__restrict__ n_due,
+                              const Counters *__restrict__ counters,
+                              unsigned long long *__restrict__ pairs) {
+    __shared__ int cnt;
+    if (threadIdx.x == 0) {
+        cnt = 0;
+        if (KICK && blockIdx.x == 0) {
+            unsigned long long sum = 0;
+            for (int c = 0; c < kCounterCopies; ++c) sum += counters[c * kCounterStride].interactions;
+            *pairs += sum;
+        }
+    }
+    if (DRIFT) __syncthreads();
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    bool next = false;
+    if (i < n) {
+        double v[3];
+        for (int d = 0; d < 3; ++d) v[d] = vel[3 * (size_t)i + d];
+        if (KICK && due[i]) {
+            kick(v, acc, i, t, k, rung, t_q, t_next);
+            for (int d = 0; d < 3; ++d) vel[3 * (size_t)i + d] = v[d];
+        }
+        if (DRIFT) {
+            for (int d = 0; d < 3; ++d) {
+                double x = pos[3 * (size_t)i + d] + v[d] * tau;
+                double r = fmod(x, box);
+                if (r < 0.0) r += box;
+                if (r >= box) r -= box;
+                pos[3 * (size_t)i + d] = r;
+            }
+            next = t_next[i] == t + 2;
+            due[i] = (uint8_t)next;
+        }
+    }
+    if (DRIFT) {
+        const unsigned long long b = __ballot(next);
+        if (b && (threadIdx.x & (kWave - 1)) == 0) atomicAdd(&cnt, __popcll(b));
+        __syncthreads();
+        if (threadIdx.x == 0 && cnt) atomicAdd(n_due, cnt);
+    }
+}
+
 // y += a x over n x 3 values (long-range kicks; summing the two force halves)
 __global__ void k_axpy3(double *__restrict__ vel, const double *__restrict__ acc, size_t n3,
                         double dk) {
@@ -127,8 +166,7 @@ __global__ void k_axpy3(double *__restrict__ vel, const double *__restrict__ acc
     vel[j] = vel[j] + acc[j] * dk;
 }
 
-// Adds one force call's accepted-pair count (the sum of its counter copies)
-// to the period's total.
+// The first force call's accepted pairs (the sum of its counter copies).
 __global__ void k_kdk_accum(const Counters *__restrict__ c, unsigned long long *__restrict__ total) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         unsigned long long s = 0;
@@ -142,9 +180,9 @@ unsigned blocks(size_t n) { return (unsigned)((n + 255) / 256); }
 }  // namespace
 
 hipError_t launch_kdk_assign(const double *acc, int n, const KdkArgs &k, uint8_t *rung,
-                             int *max_rung, hipStream_t s) {
+                             int *census, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    k_kdk_assign<<<blocks(n), 256, 0, s>>>(acc, n, k, rung, max_rung);
+    k_kdk_assign<<<(unsigned)((n + 1023) / 1024), 1024, 0, s>>>(acc, n, k, rung, census);
     return hipGetLastError();
 }
 
@@ -155,25 +193,15 @@ hipError_t launch_kdk_first(double *vel, const double *acc, int n, const KdkArgs
     return hipGetLastError();
 }
 
-hipError_t launch_kdk_drift(double *pos, const double *vel, int n, double tau, double box,
-                            hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    k_kdk_drift<<<blocks(3 * (size_t)n), 256, 0, s>>>(pos, vel, 3 * (size_t)n, tau, box);
-    return hipGetLastError();
-}
-
-hipError_t launch_kdk_due(const int *t_next, int n, int t, uint8_t *due, int *n_due,
-                          hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    k_kdk_due<<<blocks(n), 256, 0, s>>>(t_next, n, t, due, n_due);
-    return hipGetLastError();
-}
-
-hipError_t launch_kdk_kick(double *vel, const double *acc, const uint8_t *due, int n, int t,
-                           const KdkArgs &k, uint8_t *rung, int *t_q, int *t_next,
-                           hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    k_kdk_kick<<<blocks(n), 256, 0, s>>>(vel, acc, due, n, t, k, rung, t_q, t_next);
+hipError_t launch_kdk_advance(const KdkAdvance &a, bool kick, bool drift, int t, const KdkArgs &k,
+                              int *n_due, hipStream_t s) {
+    if (a.n == 0) return hipSuccess;
+    auto fn = !kick ? k_kdk_advance<false, true>
+              : drift ? k_kdk_advance<true, true>
+                      : k_kdk_advance<true, false>;
+    fn<<<(unsigned)((a.n + 1023) / 1024), 1024, 0, s>>>(a.pos, a.vel, a.acc, a.due, a.n, t, k, a.tau,
+                                                       a.box, a.rung, a.t_q, a.t_next, n_due,
+                                                       a.counters, a.pairs);
     return hipGetLastError();
 }
 

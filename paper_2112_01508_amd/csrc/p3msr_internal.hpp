@@ -498,17 +498,25 @@ struct KdkArgs {
     int max_rung;
     int fixed;            // 1: rungs are inputs and never change
 };
+// census (9 ints, zeroed): particles per rung 0 .. 7, and the highest rung
 hipError_t launch_kdk_assign(const double *acc, int n, const KdkArgs &k, uint8_t *rung,
-                             int *max_rung, hipStream_t s);
+                             int *census, hipStream_t s);
 hipError_t launch_kdk_first(double *vel, const double *acc, int n, const KdkArgs &k,
                             const uint8_t *rung, int *t_q, int *t_next, hipStream_t s);
-hipError_t launch_kdk_drift(double *pos, const double *vel, int n, double tau, double box,
-                            hipStream_t s);
-hipError_t launch_kdk_due(const int *t_next, int n, int t, uint8_t *due, int *n_due,
-                          hipStream_t s);
-hipError_t launch_kdk_kick(double *vel, const double *acc, const uint8_t *due, int n, int t,
-                           const KdkArgs &k, uint8_t *rung, int *t_q, int *t_next,
-                           hipStream_t s);
+struct KdkAdvance {
+    double *pos, *vel;
+    const double *acc;
+    uint8_t *due, *rung;
+    int *t_q, *t_next;
+    int n;
+    double tau, box;
+    const Counters *counters;        // of the force call before a kick
+    unsigned long long *pairs;       // the period's accepted pairs
+};
+// kick: the particles due at t; drift: over tau to t + 2, the particles due
+// there marked and counted in *n_due (zeroed)
+hipError_t launch_kdk_advance(const KdkAdvance &a, bool kick, bool drift, int t, const KdkArgs &k,
+                              int *n_due, hipStream_t s);
 // vel += dk acc over n x 3 values
 hipError_t launch_axpy3(double *vel, const double *acc, int n, double dk, hipStream_t s);
 hipError_t launch_kdk_accum(const Counters *c, unsigned long long *total, hipStream_t s);
