@@ -751,8 +751,9 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     int *back_ctr = (int *)(back + back_total);
     unsigned long long *stall = &counters->scan_stall;
     int *bsum = (int *)w.bsum.p;
-    P3M_HIP(launch_keys(r.pos, n, g, key, rank, cells, s));
-    P3M_HIP(launch_scan1(cells, cells, ncells, back, back_ctr, stall, bsum, s));
+    P3M_HIP(launch_keys(r.pos, n, g, key, rank, cells, back_ctr + 3, s));
+    if (!keys_scan_cells(ncells))
+        P3M_HIP(launch_scan1(cells, cells, ncells, back, back_ctr, stall, bsum, s));
     if (det) {
         // ranks in (fine sub-cell, index) order instead of the atomics' order
         unsigned long long *k64 = (unsigned long long *)w.det_k.p;

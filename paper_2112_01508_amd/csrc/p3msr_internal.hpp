@@ -273,9 +273,12 @@ inline int keys_per_thread(int n) {
 // sort.hip
 hipError_t launch_fill_i32(int *p, int v, size_t n, hipStream_t s);
 hipError_t launch_fill_f64(double *p, double v, size_t n, hipStream_t s);
-// cell key and rank inside the cell of every particle (cell_count zeroed)
+// cell key and rank inside the cell of every particle (cell_count and *done
+// zeroed); where keys_scan_cells(cells), cell_count is also scanned, as
+// launch_scan1 leaves it
+bool keys_scan_cells(size_t ncells);
 hipError_t launch_keys(const double *pos, int n, const Geom &g, int *key, int *rank,
-                       int *cell_count, hipStream_t s);
+                       int *cell_count, int *done, hipStream_t s);
 size_t scan_block_sums_needed(size_t n);
 // exclusive scan of n int32 values; out has n+1 entries (out[n] = total).
 // in may equal out.

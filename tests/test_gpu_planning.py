@@ -39,7 +39,8 @@ def _check(env, pos, active, r_cut, prec, cfg, mass=None):
         assert np.all(acc[active == 0] == 0)
 
 
-@pytest.mark.parametrize("nt", [4, 5, 25, 26])   # 64 and 125 tiles; 15625 and 17576
+# 64 and 125 tiles; 4096 and 4913 (the key kernel scans up to 4096 cells); 15625 and 17576
+@pytest.mark.parametrize("nt", [4, 5, 16, 17, 25, 26])
 @pytest.mark.parametrize("masked", [False, True])
 @pytest.mark.parametrize("cfg", [dict(subtiles_per_dim=1, item_target=64, cluster_size=8, screen=1),
                                  dict(subtiles_per_dim=2, item_target=128, cluster_size=16, screen=2)])
