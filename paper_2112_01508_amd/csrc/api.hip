@@ -537,8 +537,10 @@ constexpr double kBsplinePerPlummer = 2.8;
 //     (4096: 0.052 against 0.050 ms).
 //   - FP32 stays on the ordered kernels, which take the separation in FP64;
 //     clusters of 32 (2^21: 2.57 ms, of 16 2.63 ms, of 64 directly 4.19 ms).
-//     The adjoint, whose list entries are larger, takes 16 (2^21 FP32: 4.42
-//     against 4.60 ms).
+//   - The FP32 adjoint keeps 64-receiver clusters that walk their suppliers
+//     directly, with finer subtiles in fuller tiles: its pair term is rounded
+//     differently in the screened loops (the compiler contracts r . v in
+//     another order there), so they are left to calls that ask for them.
 //   - Receivers under a mask are sparse, so clusters of 8 (a fifth active of
 //     2^21, FP32: 1.15 ms, of 64 directly 2.50 ms; a fiftieth: 0.50, of 16
 //     0.56, of 64 directly 1.14 ms); nested rung subsets, dense and sparse in
@@ -549,16 +551,21 @@ constexpr double kBsplinePerPlummer = 2.8;
 //     (300007 FP32: 0.293 ms at 1024, 0.339 at 256; 2^21: 2.57 ms at 4096,
 //     2.70 at 512).
 struct Layout {
-    int target, csize, screen;
+    int target, csize, screen, ns;
 };
-Layout default_layout(int64_t n, bool fp32, bool backward, int sel_kind, bool mutual_ok) {
+Layout default_layout(int64_t n, int nt, bool fp32, bool backward, int sel_kind, bool mutual_ok) {
+    if (fp32 && backward) {
+        const double per_tile = (double)n / ((double)nt * nt * nt);
+        return Layout{1024, 64, 0, per_tile > 64 ? 4 : (per_tile > 8 ? 3 : 2)};
+    }
     Layout l;
+    l.ns = 1;
     l.screen = !fp32 && mutual_ok && n >= 8192 ? kScreenMutual : 1;
     const bool masked = !backward && sel_kind == SEL_MASK;
     if (l.screen == kScreenMutual) l.csize = 16;
     else if (masked) l.csize = 8;
     else if (!backward && sel_kind == SEL_RUNG) l.csize = 32;
-    else l.csize = fp32 && !backward && n >= 8192 ? 32 : 16;
+    else l.csize = fp32 && n >= 8192 ? 32 : 16;
     if (n < (1 << 14)) l.target = 128;
     else if (l.screen == kScreenMutual) l.target = (int)std::min<int64_t>(std::max<int64_t>(n >> 10, 512), 4096);
     else if (n < (1 << 16)) l.target = 256;
@@ -623,9 +630,9 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     if (r.force_screen > 0) screen = r.force_screen - 1;
     // the fixed workspace holds the mutual kernel's sums beside everything
     // else it held for a call up to half its particle limit
-    const Layout def = default_layout(r.n, fp32, r.backward, r.sel_kind,
+    const Layout def = default_layout(r.n, nt, fp32, r.backward, r.sel_kind,
                                       mutual_ok && !(w.base && r.n > kNoAllocMaxN / 2));
-    ns = pick_subtiles(nt, ns);
+    ns = pick_subtiles(nt, ns > 0 ? ns : def.ns);
     if (target <= 0) target = def.target;
     if (!valid_csize(csize)) csize = screen == kScreenMutual ? std::max(def.csize, 16) : def.csize;
     if (screen < 0) screen = def.screen == kScreenMutual && csize < 16 ? 1 : def.screen;

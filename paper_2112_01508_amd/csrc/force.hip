@@ -275,12 +275,9 @@ struct BwdF32 {
                                            const PairArgs &a) {
         const Geom &g = a.g;
         const float muj = mu_f32(pj.w);
-        // the FP32 contractions are spelled out: left to the compiler they
-        // differed between the loops this body is inlined in, and with them a
-        // pair's rounding between layouts
-        float vx = fmaf(muj, wkx, -(muk * wj.x));
-        float vy = fmaf(muj, wky, -(muk * wj.y));
-        float vz = fmaf(muj, wkz, -(muk * wj.z));
+        float vx = muj * wkx - muk * wj.x;
+        float vy = muj * wky - muk * wj.y;
+        float vz = muj * wkz - muk * wj.z;
         if (SOFT && r2 < g.eps_b2) {
             const double ri = rsqrt_pos(r2);
             const double ri2 = ri * ri;
@@ -304,7 +301,7 @@ struct BwdF32 {
         float phi = gu * ri2 * ri;
         float c = ri2 * fmaf(3.0f, phi, g.kbf * e);
         float fx = (float)dx, fy = (float)dy, fz = (float)dz;
-        float rv = fmaf(fz, vz, fmaf(fx, vx, fy * vy));
+        float rv = fx * vx + fy * vy + fz * vz;
         float crv = c * rv;
         ax -= (double)fmaf(phi, vx, -crv * fx);
         ay -= (double)fmaf(phi, vy, -crv * fy);
