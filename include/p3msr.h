@@ -103,8 +103,9 @@ typedef struct {
     int32_t shape;           /* p3m_shape of the FP32 forward kernel shape used */
     int64_t screened;        /* supplier records tested by the screen (0 without it) */
     double eps_b;            /* B-spline softening length of the call (0: none) */
-    int64_t fp64_steps;      /* screen 2: wavefront steps that redid a pair in the plain
-                                FP64 form (x_i - x_j) - n' box */
+    int64_t fp64_steps;      /* screen 2: wavefront steps with a pair in the plain FP64 form
+                                (x_i - x_j) - n' box: the ones that FP32 calls redid, every
+                                step of FP64 calls */
     float ms_sort;           /* the counting sort into tile -> subtile -> fine order (keys,
                                 scan, scatter, fine order), when timing is on, else -1 */
     int32_t deterministic;   /* 1: the call ran in the deterministic mode (p3m_sr_set_deterministic) */
@@ -318,19 +319,18 @@ int p3m_sr_tune_cache_check(const char *path, int *entries, int *lines);
  *                     both partners (Newton's third law, as the paper's tile
  *                     pairing in section 2.1.3, "Tiles"; the adjoint's pair
  *                     term is antisymmetric too): clusters visit the upper
- *                     half of their tile stencil, the pair arithmetic is on
- *                     coordinates relative to the cluster's centre (FP32, or
- *                     FP64 for P3M_FP64 calls, where pairs within a relative
- *                     2^-40 of r_cut^2 or much closer than the receiver's
- *                     offset are redone in the plain form) and the
- *                     reactions are added to the partners' FP64 sums;
+ *                     half of their tile stencil, the pair arithmetic is FP32
+ *                     on coordinates relative to the cluster's centre, or for
+ *                     P3M_FP64 calls FP64 on the separations of the other
+ *                     layouts, and the reactions are added to the partners'
+ *                     FP64 sums;
  *                     cluster_size must be 16, 32 or 64 (0 keeps the
  *                     automatic choice); other calls take screen 1 (or,
  *                     with an autotuned screen 2, the layout the autotuner
  *                     kept beside it); -1: automatic.
  * EINVAL outside those ranges.  Results do not depend on these settings
- * beyond FP64 summation order and, with screen 2, the rounding of the
- * separation (within the path's accuracy).
+ * beyond FP64 summation order and, for P3M_FP32 calls with screen 2, the
+ * rounding of the separation (within the path's accuracy).
  */
 int p3m_sr_set_config(p3m_sr_handle h, int subtiles_per_dim, int item_target,
                       int cluster_size, int screen);

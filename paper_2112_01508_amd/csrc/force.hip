@@ -1023,11 +1023,12 @@ void k_pairs(PairArgs a) {
 // The pair factor is the FP32 shape of FwdF32 (hardware rsqrt and the H
 // polynomial); a block's sums are FP32 over its 16 steps and then FP64.
 //
-// The FP64 kinds (forward, softened forward and adjoint of FP64 calls) keep
-// the offsets, the pair term and every sum in FP64; a rotated FP64 operand
-// takes two DPP moves, and the two rare cases are a relative 2^-40 band
-// around r_cut^2 and the same close-pair rule, redone in the plain form
-// (x_i - x_j) - n' box.
+// The FP64 kinds (forward, softened forward and adjoint of FP64 calls) take
+// the separations from the positions themselves, in the plain form
+// (x_i - x_j) - n' box of the ordered kernels, and keep the pair term and
+// every sum in FP64; a rotated FP64 operand takes two DPP moves.  Blocks with
+// entries of other images than the box itself (clusters at its faces) rotate
+// the entries' images too.
 //
 // The sums go to an FP64 array in sorted order, one component after the
 // other (three arrays of n), which a final pass writes to acc_out.
@@ -1044,8 +1045,8 @@ template <int KIND> constexpr bool kMutIsBwd = KIND == kMutBwd || KIND == kMutF6
 
 template <bool B, class T, class F> struct MutPick { using type = T; };
 template <class T, class F> struct MutPick<false, T, F> { using type = F; };
-// A list entry in the ring (offset from the cluster centre and mu), and an
-// entry's adjoint weight: FP32, or FP64 for the FP64 kinds.
+// A list entry in the ring (offset from the cluster centre, or for the FP64
+// kinds the position, and mu), and an entry's adjoint weight.
 template <int KIND> using MutEntry = typename MutPick<kMutIsF64<KIND>, double4, float4>::type;
 
 constexpr int kRing = 128;                    // list entries per wave (a ring)
@@ -1276,72 +1277,45 @@ __device__ __forceinline__ void mutual_steps(MutualLane &m, const float4 &e, con
     }
 }
 
-// The FP64 kind: this lane's receiver, its sums (FP64 throughout) and the
-// cut-off band (wave-uniform).
+// The FP64 kinds: this lane's receiver and its sums (FP64 throughout).
 struct MutualLane64 {
-    double hx, hy, hz;    // offset from the cluster centre (far away for idle lanes)
-    double ki;            // r^2 below which the separation is recomputed as the plain form
+    double x, y, z;       // position (far away for idle lanes)
     double mu;            // mu_i
-    double rlo, rhi;      // r_cut^2 (1 -+ 2^-40)
     int i_sorted;
     double ax = 0.0, ay = 0.0, az = 0.0;   // the receiver's sums
     double jx = 0.0, jy = 0.0, jz = 0.0;   // reaction on this lane's entry
     double wkx = 0.0, wky = 0.0, wkz = 0.0;   // adjoint: this receiver's w_k [k active]
 };
 
-// mutual_fp64_sep without the rounding to FP32.
-__device__ __attribute__((noinline)) double4 mutual_sep_plain(const double4 *__restrict__ sp,
-                                                              int i_sorted, int jr, double box,
-                                                              double rc2) {
-    const int j = (int)((unsigned)jr & kIdxMask);
-    const int img = (int)((unsigned)jr >> kIdxBits);
-    const double4 pi = sp[i_sorted];
-    const double4 pj = sp[j];
-    double ddx = pi.x - pj.x, ddy = pi.y - pj.y, ddz = pi.z - pj.z;
-    if (img != 13) {
-        ddx -= (double)(img / 9 - 1) * box;
-        ddy -= (double)((img / 3) % 3 - 1) * box;
-        ddz -= (double)(img % 3 - 1) * box;
-    }
-    const double r2d = dist2(ddx, ddy, ddz);
-    const bool ok = (r2d < rc2) & (r2d > 0.0);
-    return make_double4(ddx, ddy, ddz, ok ? r2d : -1.0);
-}
+// Periodic image n' of a list entry, each component -1, 0 or 1.
+struct EntryImage {
+    float x, y, z;
+};
 
 // One FP64 step: this lane's receiver against the entry S places along its
-// row.  The separation of two offsets from the cluster centre can differ
-// from the plain form (x_i - x_j) - n' box in its last bits, so pairs within
-// a relative 2^-40 of r_cut^2 and pairs closer than a tenth of the
-// receiver's offset are redone in the plain form: the accepted pairs are the
-// plain form's.
-template <int S, bool UNIT, bool SELF, bool BWD, bool SOFT>
+// row, with the separation in the plain form (x_i - x_j) - n' box, rounded as
+// in the ordered kernels (n' box is exact, so the fma rounds once, like their
+// subtraction): the accepted pairs and every pair's term are the ordered
+// kernels'.  IMG: the block holds entries of another image than the box
+// itself.  (From offsets to the cluster's centre, as the FP32 kinds take it,
+// the separation of a pair differed by up to 1e-13 of itself: uniform 32768,
+// largest error of a particle's force over the sum of its terms 2.2e-14, now
+// as the ordered kernel's 7e-16.)
+template <int S, bool UNIT, bool SELF, bool BWD, bool SOFT, bool IMG>
 __device__ __forceinline__ void mutual_step64(MutualLane64 &m, const double4 &e,
-                                              const double4 &ew, int jid, const PairArgs &a,
-                                              unsigned &cnt, unsigned &rare_n) {
+                                              const double4 &ew, const EntryImage &img,
+                                              const PairArgs &a, unsigned &cnt) {
     __builtin_amdgcn_sched_barrier(0);
-    double dx = m.hx - rot16<S>(e.x);
-    double dy = m.hy - rot16<S>(e.y);
-    double dz = m.hz - rot16<S>(e.z);
-    double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    const unsigned long long m_lo = ballot64(r2 < m.rlo);
-    const unsigned long long m_far = ballot64(r2 >= m.ki);
-    const unsigned long long m_hi = ballot64(r2 < m.rhi);
-    unsigned long long acc_m = m_lo & m_far;
-    const unsigned long long rare = (m_hi & ~m_lo) | ~m_far;
-    if (rare) {
-        const int jr = rot16i<S>(jid);   // all lanes active here
-        ++rare_n;
-        bool ok = false;
-        if ((rare >> (threadIdx.x & (kWave - 1))) & 1ull) {
-            const double4 q = mutual_sep_plain(a.sp, m.i_sorted, jr, a.g.box, a.g.rc2);
-            ok = q.w > 0.0;
-            dx = q.x;
-            dy = q.y;
-            dz = q.z;
-            r2 = ok ? q.w : 1.0;
-        }
-        acc_m = (acc_m & ~rare) | (ballot64(ok) & rare);
+    double dx = m.x - rot16<S>(e.x);
+    double dy = m.y - rot16<S>(e.y);
+    double dz = m.z - rot16<S>(e.z);
+    if constexpr (IMG) {
+        dx = fma(-(double)rot16<S>(img.x), a.g.box, dx);
+        dy = fma(-(double)rot16<S>(img.y), a.g.box, dy);
+        dz = fma(-(double)rot16<S>(img.z), a.g.box, dz);
     }
+    const double r2 = dist2(dx, dy, dz);
+    const unsigned long long acc_m = ballot64(r2 < a.g.rc2) & ballot64(r2 > 0.0);
     cnt += (unsigned)__builtin_popcountll(acc_m);
     if constexpr (BWD) {
         // the adjoint's term, as in the FP32 kind: receiver k gets -J(r) v
@@ -1413,27 +1387,27 @@ __device__ __forceinline__ void mutual_step64(MutualLane64 &m, const double4 &e,
     asm volatile("" ::"v"(m.ax), "v"(m.ay), "v"(m.az), "v"(m.jx), "v"(m.jy), "v"(m.jz));
 }
 
-template <bool UNIT, bool SELF, int NS, bool BWD, bool SOFT>
+template <bool UNIT, bool SELF, int NS, bool BWD, bool SOFT, bool IMG>
 __device__ __forceinline__ void mutual_steps64(MutualLane64 &m, const double4 &e,
-                                               const double4 &ew, int jid, const PairArgs &a,
-                                               unsigned &cnt, unsigned &rare_n) {
-    mutual_step64<0, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-    mutual_step64<1, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-    mutual_step64<2, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-    mutual_step64<3, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
+                                               const double4 &ew, const EntryImage &img,
+                                               const PairArgs &a, unsigned &cnt) {
+    mutual_step64<0, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+    mutual_step64<1, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+    mutual_step64<2, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+    mutual_step64<3, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
     if constexpr (NS > 4) {
-        mutual_step64<4, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<5, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<6, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<7, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<8, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<9, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<10, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<11, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<12, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<13, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<14, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
-        mutual_step64<15, UNIT, SELF, BWD, SOFT>(m, e, ew, jid, a, cnt, rare_n);
+        mutual_step64<4, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<5, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<6, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<7, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<8, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<9, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<10, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<11, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<12, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<13, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<14, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
+        mutual_step64<15, UNIT, SELF, BWD, SOFT, IMG>(m, e, ew, img, a, cnt);
     }
 }
 
@@ -1454,7 +1428,7 @@ struct MutualVisit {
     static constexpr int EB = 64 / R;   // list entries per block of 16 steps
     const PairArgs &a;
     Lane &m;
-    MutEntry<KIND> *lpos;   // ring: offset from the cluster centre, mu
+    MutEntry<KIND> *lpos;   // ring: offset from the cluster centre (FP64: position), mu
     int *lidx;           // ring: sorted index | image << kIdxBits
     MutEntry<KIND> *lw;   // ring (adjoint): the entry's weight w_j [j active]
     const double *lo, *hi;
@@ -1505,9 +1479,20 @@ struct MutualVisit {
         wave_lds_sync();   // the reads are done before later screens overwrite the ring
         m.jx = m.jy = m.jz = 0.f;
         unsigned cnt = 0, rn = 0;
-        if constexpr (F64)
-            mutual_steps64<UNIT, false, 16, BWD, KIND == kMutF64Soft>(m, e, ew, jid, a, cnt, rn);
-        else mutual_steps<UNIT, false, 16, KIND>(m, e, ew, jid, a, cnt, rn);
+        if constexpr (F64) {
+            constexpr bool SOFT = KIND == kMutF64Soft;
+            const int code_k = k < nv ? (int)((unsigned)jid >> kIdxBits) : 13;
+            if (ballot64(code_k != 13)) {
+                const EntryImage img{(float)(code_k / 9 - 1), (float)((code_k / 3) % 3 - 1),
+                                     (float)(code_k % 3 - 1)};
+                mutual_steps64<UNIT, false, 16, BWD, SOFT, true>(m, e, ew, img, a, cnt);
+            } else {
+                mutual_steps64<UNIT, false, 16, BWD, SOFT, false>(m, e, ew, EntryImage{}, a, cnt);
+            }
+            rn = 16;
+        } else {
+            mutual_steps<UNIT, false, 16, KIND>(m, e, ew, jid, a, cnt, rn);
+        }
         flush_i();
         const auto jx = rows_sum<R>(m.jx), jy = rows_sum<R>(m.jy), jz = rows_sum<R>(m.jz);
         if (row % R == 0 && k < nv) {
@@ -1540,7 +1525,7 @@ struct MutualVisit {
             if (idx < cnt) {
                 const double4 q = a.sp[begin + idx];
                 if constexpr (F64)
-                    e = make_double4(q.x - cx, q.y - cy, q.z - cz, UNIT ? 0.0 : q.w);
+                    e = make_double4(q.x, q.y, q.z, UNIT ? 0.0 : q.w);
                 else
                     e = make_float4((float)(q.x - cx), (float)(q.y - cy), (float)(q.z - cz),
                                     UNIT ? 0.f : mu_f32(q.w));
@@ -1548,13 +1533,17 @@ struct MutualVisit {
                 if constexpr (BWD) ew = wa_entry(begin + idx);
             }
             unsigned c = 0, rn = 0;
-            if constexpr (F64)
-                mutual_steps64<UNIT, true, R == 1 ? 4 : 16, BWD, KIND == kMutF64Soft>(m, e, ew,
-                                                                                    jid, a, c, rn);
-            else mutual_steps<UNIT, true, R == 1 ? 4 : 16, KIND>(m, e, ew, jid, a, c, rn);
+            constexpr int NS = R == 1 ? 4 : 16;
+            if constexpr (F64) {
+                mutual_steps64<UNIT, true, NS, BWD, KIND == kMutF64Soft, false>(
+                    m, e, ew, EntryImage{}, a, c);
+                rn = NS;
+            } else {
+                mutual_steps<UNIT, true, NS, KIND>(m, e, ew, jid, a, c, rn);
+            }
             flush_i();
             pairs += c;
-            steps += R == 1 ? 4 : 16;
+            steps += NS;
             rare += rn;
         }
     }
@@ -1575,7 +1564,7 @@ struct MutualVisit {
         if (keep) {
             const int q = (head + n_list + off) & (kRing - 1);
             if constexpr (F64)
-                lpos[q] = make_double4(px - cx, py - cy, pz - cz, UNIT ? 0.0 : p.w);
+                lpos[q] = make_double4(p.x, p.y, p.z, UNIT ? 0.0 : p.w);
             else
                 lpos[q] = make_float4((float)(px - cx), (float)(py - cy), (float)(pz - cz),
                                       UNIT ? 0.f : mu_f32(p.w));
@@ -1657,17 +1646,10 @@ __device__ __forceinline__ void mutual_item(const PairArgs &a, const Item &item,
     m.i_sorted = begin + (live ? idx : 0);
     const double4 xp = a.sp[m.i_sorted];
     if constexpr (F64) {
-        m.hx = live ? xp.x - cx : 1.0e30;
-        m.hy = live ? xp.y - cy : 1.0e30;
-        m.hz = live ? xp.z - cz : 1.0e30;
+        m.x = live ? xp.x : 1.0e30;
+        m.y = live ? xp.y : 1.0e30;
+        m.z = live ? xp.z : 1.0e30;
         m.mu = xp.w;
-        // separations below a tenth of the receiver's offset take the plain
-        // form (and r^2 == 0, since ki is at least the smallest normal)
-        m.ki = live ? fmax(0.01 * fma(m.hz, m.hz, fma(m.hy, m.hy, m.hx * m.hx)),
-                           2.2250738585072014e-308)
-                    : 0.0;
-        m.rlo = a.g.rc2 * (1.0 - 0x1p-40);
-        m.rhi = a.g.rc2 * (1.0 + 0x1p-40);
     } else {
         m.hx = live ? (float)(xp.x - cx) : 1.0e30f;
         m.hy = live ? (float)(xp.y - cy) : 1.0e30f;
