@@ -1336,14 +1336,15 @@ __device__ __forceinline__ void mutual_step64(MutualLane64 &m, const double4 &e,
         const double ri2 = ri * ri;
         double dh;
         const double h = h64_d(fma(r2, a.g.c2, -P3M_H64_T0), a.g.h64, dh);
-        // lanes without a pair give no term
-        const double phi = keep_lanes(acc_m, fma(a.g.c3, h, ri2 * ri));
-        const double c =
-            keep_lanes(acc_m, fma(3.0 * ri2 * ri2, ri, -2.0 * a.g.c2 * a.g.c3 * dh));
+        const double phi = fma(a.g.c3, h, ri2 * ri);
+        const double c = fma(3.0 * ri2 * ri2, ri, -2.0 * a.g.c2 * a.g.c3 * dh);
         const double crv = c * fma(dz, vz, fma(dy, vy, dx * vx));
-        const double ox = fma(-crv, dx, phi * vx);
-        const double oy = fma(-crv, dy, phi * vy);
-        const double oz = fma(-crv, dz, phi * vz);
+        // lanes without a pair give no term; masked here and not before v
+        // enters: 0 times an infinite or NaN weight is NaN, and would reach
+        // particles beyond r_cut
+        const double ox = keep_lanes(acc_m, fma(-crv, dx, phi * vx));
+        const double oy = keep_lanes(acc_m, fma(-crv, dy, phi * vy));
+        const double oz = keep_lanes(acc_m, fma(-crv, dz, phi * vz));
         m.ax -= ox;
         m.ay -= oy;
         m.az -= oz;
@@ -1368,12 +1369,14 @@ __device__ __forceinline__ void mutual_step64(MutualLane64 &m, const double4 &e,
                 shv = fma(a.g.c3, h, bspline_m3(r2 * ri * a.g.inv_eps_b, ri3, a.g));
         }
     }
-    // lanes without a pair send no reaction
-    const double sh = keep_lanes(acc_m, shv);
-    double shj = sh, shi = sh;
-    if constexpr (!UNIT) {
-        shj = sh * rot16<S>(e.w);
-        shi = sh * m.mu;
+    // lanes without a pair send no reaction (masked after the masses enter,
+    // as in the adjoint)
+    double shj, shi;
+    if constexpr (UNIT) {
+        shj = shi = keep_lanes(acc_m, shv);
+    } else {
+        shj = keep_lanes(acc_m, shv * rot16<S>(e.w));
+        shi = keep_lanes(acc_m, shv * m.mu);
     }
     const double fx = shi * dx, fy = shi * dy, fz = shi * dz;
     m.ax = fma(-shj, dx, m.ax);
