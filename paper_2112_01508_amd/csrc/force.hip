@@ -1440,6 +1440,7 @@ struct MutualVisit {
     int own_from;        // own tile: suppliers from this sorted index on
     double ax = 0.0, ay = 0.0, az = 0.0;
     unsigned long long pairs = 0, steps = 0, screened = 0, rare = 0;
+    unsigned long long listed = 0;   // list entries met (counted by the FP64 kinds)
     bool own = false;
     int code = 13;
     double shx = 0.0, shy = 0.0, shz = 0.0;
@@ -1493,6 +1494,7 @@ struct MutualVisit {
                 mutual_steps64<UNIT, false, 16, BWD, SOFT, false>(m, e, ew, EntryImage{}, a, cnt);
             }
             rn = 16;
+            listed += nv;
         } else {
             mutual_steps<UNIT, false, 16, KIND>(m, e, ew, jid, a, cnt, rn);
         }
@@ -1628,7 +1630,7 @@ struct MutualVisit {
 
 // Tallies of a wave's items.
 struct MutualTally {
-    unsigned long long pairs = 0, steps = 0, screened = 0, rare = 0;
+    unsigned long long pairs = 0, steps = 0, screened = 0, rare = 0, cand = 0;
 };
 
 // One work item in the layout of R rows per receiver copy (cnt <= 16 R).
@@ -1702,6 +1704,10 @@ __device__ __forceinline__ void mutual_item(const PairArgs &a, const Item &item,
     tally.steps += v.steps;
     tally.screened += v.screened;
     tally.rare += v.rare;
+    // (receiver, supplier) pairs: both directions of a listed entry
+    if constexpr (F64)
+        tally.cand += (unsigned long long)cnt *
+                      (2 * v.listed + (item.sole & kItemFirst ? (unsigned long long)cnt : 0ull));
 }
 
 // The persistent kernel of the mutual evaluation: clusters of up to 16 RMAX
@@ -1747,7 +1753,7 @@ void k_pairs_mutual(PairArgs a) {
         mutual_item<RMAX, UNIT, KIND>(a, item, cl, cnt, begin, lane, ring_pos[w], ring_idx[w],
                                      ring_wt[BWD ? w : 0], tally);
     }
-    add_counts(a, lane, tally.pairs, 0, tally.steps, tally.screened, tally.rare);
+    add_counts(a, lane, tally.pairs, tally.cand, tally.steps, tally.screened, tally.rare);
 }
 
 // acc_out[3 perm[p] + c] = sums[c n + p]
