@@ -33,7 +33,9 @@
  *     mode, and layouts whose item bound passes 1 GiB (large rung-batched
  *     calls with several subtiles per tile).  A call that grows the
  *     workspace waits for the stream before freeing the old buffer.
- *   - Outputs are fully overwritten (rows of non-receivers become 0).
+ *   - Outputs are fully overwritten (rows of non-receivers become 0).  The
+ *     output of a force, backward or batched call may overlap the call's
+ *     inputs: they are read before it is written.
  *   - Errors return a negative code, leave outputs untouched when detected
  *     before any launch, and set a per-thread message (p3m_sr_last_error).
  *   - A handle is not thread-safe: use one handle per host thread.

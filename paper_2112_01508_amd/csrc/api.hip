@@ -573,6 +573,17 @@ Layout default_layout(int64_t n, int nt, bool fp32, bool backward, int sel_kind,
     return l;
 }
 
+// The output of a call and one of its inputs share bytes.
+bool output_over_input(const Request &r) {
+    const size_t n = (size_t)r.n;
+    const uintptr_t o0 = (uintptr_t)r.out, o1 = o0 + sizeof(double) * 3 * n * (size_t)r.n_sub;
+    auto over = [&](const void *p, size_t bytes) {
+        return p && (uintptr_t)p < o1 && o0 < (uintptr_t)p + bytes;
+    };
+    return over(r.pos, sizeof(double) * 3 * n) || over(r.mass, sizeof(double) * n) ||
+           over(r.sel, n) || over(r.grad_acc, sizeof(double) * 3 * n);
+}
+
 int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     hipStream_t s = r.stream;
     const int n = (int)r.n;
@@ -740,6 +751,8 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     // ---- sort ----
     int *fbig = (int *)w.fbig.p;
     double4 *sp_f = (double4 *)w.sp2.p;   // the sorted particles after the fine order
+    // an output over an input is cleared after the inputs' last reader
+    const bool clear_late = !mutual && output_over_input(r);
     {
         // everything the call clears, in one launch: the output too (the
         // mutual kernel's sorted-order sums)
@@ -751,7 +764,7 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
         f.add((int *)(sp_f + n), kSupplierPad * sizeof(double4) / sizeof(int), 0);
         f.add((int *)w.back.p, 2 * back_total + 4, 0);
         if (mutual) f.add((int *)w.msum.p, 6 * (size_t)n, 0);
-        else f.add((int *)r.out, 2 * out_elems, 0);
+        else if (!clear_late) f.add((int *)r.out, 2 * out_elems, 0);
         P3M_HIP(launch_fill_multi(f, s));
     }
     unsigned long long *back = (unsigned long long *)w.back.p;
@@ -838,6 +851,7 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     }
     P3M_HIP(launch_cluster_finish(clusters, n_clusters, cl_bound, csize, rp, r.grad_acc, sel_s, perm,
                                   fp32 ? 1 : 0, wa, s));
+    if (clear_late) P3M_HIP(launch_fill_f64(r.out, 0.0, out_elems, s));
     if (shape != SHAPE_POLY)
         P3M_HIP(launch_build_htab(shape, h->cfg_tab_n, g, (float *)w.htab.p, s));
     Item *items = (Item *)w.items.p;
@@ -1915,6 +1929,9 @@ int p3m_force(p3m_sr_handle h, const double *pos, const double *mass, const uint
     r.precision = precision;
     r.out = acc_out;
     r.stream = s;
+    // an output over an input: the long range, which reads the inputs on its
+    // own stream, comes first
+    if (output_over_input(r)) P3M_HIP(hipStreamWaitEvent(s, h->join_ev, 0));
     rc = run(h, r, h->work);
     // join before returning, also when the short range failed
     P3M_HIP(hipStreamWaitEvent(s, h->join_ev, 0));
