@@ -182,7 +182,9 @@ struct p3m_sr_context {
     // long-range PM workspace and timing
     DevBuf pm_real, pm_spec, pm_tab, pm_key, pm_rank, pm_bins, pm_rec, pm_nkey, pm_perm, pm_bsum,
         p3m_lr, tune_w, tune_sig;
-    unsigned long long *pm_stall = nullptr;   // the bin scan's give-up count (in pm_bins)
+    // the bin scan's give-up count of the last long-range call: a buffer of
+    // its own, of one size, so that it outlives calls that fail to grow theirs
+    DevBuf pm_stall;
     // p3m_force: the long-range half runs on this stream beside the short range
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
@@ -953,8 +955,9 @@ int lr_run(p3m_sr_context *h, const double *pos, const double *mass, const uint8
     if ((rc = ensure(h, h->pm_rec, np1 * sizeof(double4), s))) return rc;
     if ((rc = ensure(h, h->pm_nkey, np1 * sizeof(int), s))) return rc;
     if ((rc = ensure(h, h->pm_perm, np1 * sizeof(int), s))) return rc;
-    const PmSort ps = pm_sort_layout((int *)h->pm_bins.p, n_grid, np);
-    h->pm_stall = ps.stall;
+    if ((rc = ensure(h, h->pm_stall, sizeof(unsigned long long), s))) return rc;
+    PmSort ps = pm_sort_layout((int *)h->pm_bins.p, n_grid, np);
+    ps.stall = (unsigned long long *)h->pm_stall.p;
     h->last_stream = s;
     double2 *tw = (double2 *)h->pm_tab.p;
     double *w1 = (double *)(tw + g / 2);
@@ -1065,7 +1068,7 @@ int p3m_sr_destroy(p3m_sr_handle h) {
                       &w.msum,    &w.htab,    &w.det_k,    &w.det_v,    &w.det_hist,
                       &w.partials, &w.back,
                       &h->pm_real, &h->pm_spec, &h->pm_tab, &h->pm_key,  &h->pm_rank,
-                      &h->pm_bins, &h->pm_rec,  &h->pm_nkey, &h->pm_perm,
+                      &h->pm_bins, &h->pm_rec,  &h->pm_nkey, &h->pm_perm, &h->pm_stall,
                       &h->kdk_acc, &h->kdk_lr,  &h->kdk_tq,  &h->kdk_tnext, &h->kdk_due,
                       &h->kdk_scal, &h->pm_bsum, &h->p3m_lr, &h->tune_w, &h->tune_sig};
     for (DevBuf *b : bufs)
@@ -1699,9 +1702,9 @@ int p3m_lr_get_stats(p3m_sr_handle h, p3m_lr_stats *out) {
     } else if (h->lr_stream || st.n > 0) {
         P3M_HIP(hipStreamSynchronize(h->lr_stream));
     }
-    if (h->pm_stall && st.n > 0) {
+    if (h->pm_stall.p && st.n > 0) {
         unsigned long long stalled = 0;
-        P3M_HIP(hipMemcpy(&stalled, h->pm_stall, sizeof(stalled), hipMemcpyDeviceToHost));
+        P3M_HIP(hipMemcpy(&stalled, h->pm_stall.p, sizeof(stalled), hipMemcpyDeviceToHost));
         if (stalled)
             return set_error(P3M_EHIP, "the bin scan of the last call waited past its poll limit "
                                        "(its result is not valid)");

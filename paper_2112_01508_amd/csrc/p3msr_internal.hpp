@@ -455,7 +455,7 @@ struct PmSort {
     int *start;                   // (n / kPmBin)^3 + 1
     int *over;                    // runs of dense bins: their number, then (bin, first) pairs
     unsigned long long *status;   // the scan's look-back words
-    unsigned long long *stall;
+    unsigned long long *stall;    // not in the array: set by the caller
     int *ctr;
     size_t ints;                  // the array's length
 };

@@ -247,10 +247,12 @@ __global__ __launch_bounds__(256) void k_pm_deposit_over(const double4 *__restri
 }
 
 // Twiddles tw[m] = exp(-2 pi i m / n), m < n/2, the kernel tables, and the
-// sort array cleared (16-byte stores; its length is a multiple of 4 ints).
+// sort array (16-byte stores; its length is a multiple of 4 ints) and *stall
+// cleared.
 __global__ void k_pm_prepare(int n, double box, double x_s, double2 *tw, double *w1, double *k2,
-                             int4 *zero, size_t n4) {
+                             int4 *zero, size_t n4, unsigned long long *stall) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *stall = 0;
     for (size_t j = i; j < n4; j += (size_t)gridDim.x * blockDim.x) zero[j] = make_int4(0, 0, 0, 0);
     if (i < n / 2) {
         double s, c;
@@ -623,8 +625,7 @@ PmSort pm_sort_layout(int *bins, int n, int n_part) {
     at += even(1 + 2 * ((size_t)n_part / kOverRun + 1));
     p.status = (unsigned long long *)(bins + at);
     at += even(2 * scan1_status_needed(cells));
-    p.stall = (unsigned long long *)(bins + at);
-    p.ctr = bins + at + 2;
+    p.ctr = bins + at;
     p.ints = at + 4;
     return p;
 }
@@ -636,7 +637,7 @@ hipError_t launch_pm_prepare(int n, double box, double x_s, double2 *tw, double 
     const unsigned grid = (unsigned)(blocks < (size_t)n / 256 + 1 ? n / 256 + 1
                                      : blocks > 4096              ? 4096
                                                                   : blocks);
-    k_pm_prepare<<<grid, 256, 0, s>>>(n, box, x_s, tw, w1, k2, (int4 *)ps.start, n4);
+    k_pm_prepare<<<grid, 256, 0, s>>>(n, box, x_s, tw, w1, k2, (int4 *)ps.start, n4, ps.stall);
     return hipGetLastError();
 }
 
