@@ -511,6 +511,7 @@ struct DirectVisit {
     WaveCounts &wc;
     bool shifted = false;
     double shx = 0.0, shy = 0.0, shz = 0.0;
+    __device__ __forceinline__ int first(int j0) const { return j0; }
     __device__ __forceinline__ void tile(int, int, bool sh, double x, double y, double z) {
         shifted = sh;
         shx = x;
@@ -606,6 +607,7 @@ struct ScreenVisit {
         fill = 0;
         if (n_list > CAP - kWave) flush();   // keeps n_list <= CAP
     }
+    __device__ __forceinline__ int first(int j0) const { return j0; }
     __device__ __forceinline__ void tile(int, int img, bool, double x, double y, double z) {
         if (img != code) {
             screen_chunk();
@@ -660,7 +662,8 @@ __device__ __forceinline__ void walk_item(Visit &v, const Item &item, const Clus
     const double *lo = cl.lo, *hi = cl.hi;
     const int tx = cl.tile / (g.nt * g.nt), ty = (cl.tile / g.nt) % g.nt, tz = cl.tile % g.nt;
     const int t0 = item.tiles & 0xff, t1 = (item.tiles >> 8) & 0xff;
-    // kItemPart: run `part` of `parts` equal runs of the tile's records
+    // kItemPart: run `part` of `parts` equal runs of the records that the
+    // visitor takes of the tile
     const bool split = (item.sole & kItemPart) != 0;
     const int part = item.subs & 0xffff, parts = (item.subs >> 16) & 0xffff;
     const int s0 = split ? 0 : part, s1 = split ? 1 : parts;
@@ -719,10 +722,10 @@ __device__ __forceinline__ void walk_item(Visit &v, const Item &item, const Clus
                 const int ra = __builtin_ctzll(m);
                 const unsigned long long rest = ~(m >> ra);
                 const int rb = rest ? ra + __builtin_ctzll(rest) : kWave;   // run [ra, rb)
-                int j0 = __builtin_amdgcn_readlane(cst, ra);
+                int j0 = v.first(__builtin_amdgcn_readlane(cst, ra));
                 int j1 = __builtin_amdgcn_readlane(cen, rb - 1);
                 if (split) {
-                    const long long len = j1 - j0;
+                    const long long len = max(j1 - j0, 0);
                     j1 = j0 + (int)(len * (part + 1) / parts);
                     j0 += (int)(len * part / parts);
                 }
@@ -1594,6 +1597,9 @@ struct MutualVisit {
             return *r;
         }
     }
+    // the first record taken of a run that starts at j0: in the own tile the
+    // cluster's partners are the particles after it
+    __device__ __forceinline__ int first(int j0) const { return own ? max(j0, own_from) : j0; }
     __device__ __forceinline__ void tile(int t, int img, bool, double x, double y, double z) {
         own = t == 13;
         if (img != code) {
@@ -1607,8 +1613,6 @@ struct MutualVisit {
     __device__ __forceinline__ void run(int j0, int j1) {
         j0 = __builtin_amdgcn_readfirstlane(j0);
         j1 = __builtin_amdgcn_readfirstlane(j1);
-        if (own) j0 = max(j0, own_from);
-        if (j0 >= j1) return;
         screened += (unsigned long long)(j1 - j0);
         while (j0 < j1) {
             if (lane >= fill) jj = j0 - fill;
