@@ -709,7 +709,8 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     // the call's look-back launches (cell scan, receivers, plan)
     const size_t back_cells = scan1_status_needed(ncells);
     const size_t back_recv = all_recv ? 0 : receivers_status_needed(rows);
-    const size_t back_total = back_cells + back_recv + plan_status_needed(n_sub, g);
+    const size_t back_plan = plan_status_needed(n_sub, g);
+    const size_t back_total = back_cells + back_recv + back_plan;
     if ((rc = take(h, w, w.back, sizeof(unsigned long long) * back_total + 4 * sizeof(int), s)))
         return rc;
     if (det) {
@@ -725,18 +726,32 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     // the fixed workspace), or in the deterministic mode, whose partial slots
     // are per item: then the host waits for the count (below)
     // Dense tiles of one subtile are split in small sets, where the array
-    // still holds the items without asking for their number.
-    size_t item_bound = cl_bound * (size_t)plan_items_bound(g.ns3, mutual ? 1 : 0);
-    const size_t split_bound =
-        item_bound + (size_t)n_sub * (size_t)split_items_bound(n, csize, target);
-    const size_t room = w.base ? (w.size - w.used) / sizeof(Item) : kItemBoundBytes / sizeof(Item);
-    const int split = g.ns3 == 1 && n <= kSplitMax && split_bound + 16 <= room ? 1 : 0;
-    if (split) item_bound = split_bound;
+    // still holds the items without asking for their number, and where the
+    // memory for it is there: what an unsplit plan needs is always enough.
+    const size_t plain_bound = cl_bound * (size_t)plan_items_bound(g.ns3, mutual ? 1 : 0);
+    size_t item_bound = plain_bound;
+    int split = 0;
+    if (g.ns3 == 1 && n <= kSplitMax) {
+        const int run_of = split_run(n, target);
+        const size_t bound = plain_bound + (size_t)n_sub * (size_t)split_items_bound(n, csize, run_of);
+        const size_t room = (w.base ? w.size - w.used : kItemBoundBytes) / sizeof(Item);
+        if (bound + 16 <= room) {
+            split = run_of;
+            item_bound = bound;
+        }
+    }
     bool wait_count = det || item_bound * sizeof(Item) > kItemBoundBytes ||
                       item_bound > (size_t)INT_MAX;
     if (!wait_count && w.base && w.used + item_bound * sizeof(Item) + 256 > w.size)
         wait_count = true;
-    if (!wait_count && (rc = take(h, w, w.items, sizeof(Item) * item_bound, s))) return rc;
+    if (!wait_count) {
+        rc = take(h, w, w.items, sizeof(Item) * item_bound, s);
+        if (rc == P3M_ENOMEM && split) {
+            split = 0;
+            rc = take(h, w, w.items, sizeof(Item) * plain_bound, s);
+        }
+        if (rc) return rc;
+    }
     if (wait_count && (rc = take(h, w, w.itemoff, sizeof(int) * (cl_bound + 1), s))) return rc;
 
     int *key = (int *)w.key.p, *rank = (int *)w.rank.p, *cells = (int *)w.cells.p;
@@ -840,17 +855,29 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
         pa.n_items = n_items;
         pa.host_tot = h->host_tot;
         P3M_HIP(launch_plan(pa, g, s));
+        while (wait_count) {
+            P3M_HIP(hipEventRecord(h->tot_ev, s));
+            P3M_HIP(hipEventSynchronize(h->tot_ev));
+            const size_t count = (size_t)std::max(h->host_tot[2], 1);
+            const size_t used = w.used;
+            rc = take(h, w, w.items, sizeof(Item) * count, s);
+            if (!rc && det)
+                rc = take(h, w, w.partials, sizeof(double) * 3 * (size_t)csize * count, s);
+            if (!rc) break;
+            if (!pa.split || (rc != P3M_ENOMEM && rc != P3M_EUNSUPPORTED)) return rc;
+            // the split plan's items or partial slots do not fit: plan again, unsplit
+            w.used = used;
+            pa.split = split = 0;
+            FillSet f{};
+            f.add((int *)pa.status, 2 * back_plan, 0);
+            f.add(pa.ctr, 1, 0);
+            P3M_HIP(launch_fill_multi(f, s));
+            P3M_HIP(launch_plan(pa, g, s));
+        }
     }
-    if (wait_count) {
-        P3M_HIP(hipEventRecord(h->tot_ev, s));
-        P3M_HIP(hipEventSynchronize(h->tot_ev));
-        const size_t count = (size_t)std::max(h->host_tot[2], 1);
-        if ((rc = take(h, w, w.items, sizeof(Item) * count, s))) return rc;
-        if (det && (rc = take(h, w, w.partials, sizeof(double) * 3 * (size_t)csize * count, s)))
-            return rc;
+    if (wait_count)
         P3M_HIP(launch_item_write(clusters, n_clusters, (int)cl_bound, cells, g, target,
                                   mutual ? 1 : 0, split, item_off, (Item *)w.items.p, s));
-    }
     P3M_HIP(launch_cluster_finish(clusters, n_clusters, cl_bound, csize, rp, r.grad_acc, sel_s, perm,
                                   fp32 ? 1 : 0, wa, s));
     if (clear_late) P3M_HIP(launch_fill_f64(r.out, 0.0, out_elems, s));

@@ -116,16 +116,21 @@ enum SelKind { SEL_ALL = 0, SEL_MASK = 1, SEL_RUNG = 2 };
 // Greedy grouping of the 27 neighbour tiles into items of about `target`
 // supplier candidates (before subtile culling); a tile holding more than
 // `target` particles is split by subtile ranges, or, where a tile is one
-// subtile and `split` is set, into runs of about `target` of its records.
+// subtile and `split` is not 0, into runs of about `split` of its records.
 // Without a split, at most 2 items per stencil tile plus one with one subtile
 // per tile (a flush and the tile itself), at most 1 + ns^3 per tile plus one
-// otherwise (plan_items_bound).  Splits add less than w / target items per
+// otherwise (plan_items_bound).  Splits add less than w / split items per
 // cluster and tile of w particles, and a tile is in the stencils of at most
 // 27 tiles, whose clusters number at most 27 + n / csize (split_items_bound).
 // They are for small sets (kSplitMax): a halo that holds a good part of one
 // has too few clusters to fill the GPU, and one of its items would walk the
 // whole halo (120000 particles, half of them in one tile, FP32: 8.9 ms per
-// call without, 2.9 ms with); in larger sets other clusters fill the GPU.
+// call without, 2.8 ms with); in larger sets other clusters fill the GPU.
+// A run is at least a kSplitRuns'th of the set (split_run), so the bound on
+// the items grows with the set and not with its square, which took 1 GB near
+// 2^20 particles or switched the split off (a million, 5 % of them in one tile,
+// FP64: 6.7 ms, now 3.5 ms).  With 128 runs a set of 400000 of that shape takes
+// 0.99 ms against 0.84 ms; without the limit, runs of `target`, 0.82 ms.
 //
 // HALF (pairs evaluated once, for both partners): only the upper half of the
 // stencil, t = 13 .. 26, whose periodic mirror images are the lower half; in
@@ -138,11 +143,15 @@ inline long long plan_items_bound(int ns3, int half) {
     return tiles * (ns3 == 1 ? 2 : 1 + ns3) + 2;
 }
 
-inline long long split_items_bound(long long n, int csize, int target) {
-    return (n / target) * (27 + n / csize);
-}
 constexpr int kSplitMax = 1 << 20;   // particles
-constexpr int kSplitParts = 1 << 14; // runs per tile
+constexpr int kSplitRuns = 256;
+inline int split_run(long long n, int target) {
+    const long long least = (n + kSplitRuns - 1) / kSplitRuns;
+    return target > least ? target : (int)least;
+}
+inline long long split_items_bound(long long n, int csize, int run) {
+    return (n / run) * (27 + n / csize);
+}
 
 // Particles of each stencil tile of the cluster [begin, begin + count) of
 // `tile` that the plan counts.  All loads are issued before any is used: the
@@ -180,7 +189,7 @@ __device__ __forceinline__ int plan_items(const int (&w)[27], int target, int ns
         if (w[t] > target) {
             if (acc > 0) emit(n++, t0, t, 0, ns3, 0);
             if (split) {
-                const int parts = min(w[t] / target, kSplitParts);
+                const int parts = max(w[t] / split, 1);
                 for (int q = 0; q < parts; ++q) emit(n++, t, t + 1, q, parts, kItemPart);
             } else {
                 const int parts = min((w[t] + target - 1) / target, ns3);
@@ -340,7 +349,7 @@ struct PlanArgs {
     const int *cell_start;
     const int *prefix;      // of launch_receivers; nullptr: every particle a receiver
     int n, n_sub, csize, target, half;
-    int split;              // dense tiles of one subtile into runs of records
+    int split;              // dense tiles of one subtile into runs of about this many records (0: not)
     Cluster *clusters;      // tile, subset, begin and count of every cluster
     Item *items;            // nullptr: counted only
     int *item_off;          // nullptr, or the first item of every cluster (and the total)
