@@ -134,7 +134,8 @@ typedef struct {
     int64_t n;               /* particles */
     int32_t highest_rung;    /* L: highest rung of the period (drift sub-step dt / 2^L) */
     int32_t substeps;        /* drift sub-steps: n_steps 2^L */
-    int32_t sr_calls;        /* short-range force evaluations (the start + sub-steps with kicks) */
+    int32_t sr_calls;        /* short-range force evaluations (the start + sub-steps with kicks;
+                                a call queued for a sub-step that had none is not counted) */
     int32_t lr_calls;        /* long-range force evaluations (rung-0 kicks) */
     float ms_total;          /* whole call (GPU side), when timing is on, else -1 */
     int32_t pad;
@@ -495,7 +496,10 @@ int p3m_force(p3m_sr_handle h, const double *pos, const double *mass, const uint
  *             Plummer-equivalent softening length (also the softening of the
  *             short-range force; eps > 0 unless rungs are fixed).
  *   max_rung  0..7 (the paper's default maximum of 8 rungs).
- * Synchronises with the host once per sub-step.  Errors: those of
+ * Synchronises with the host at the start, for the rungs, and at the end.
+ * Where rungs can change and fewer than 64 particles start on rung L, or, in
+ * sets above 2^17, once a sub-step had none to kick, it asks before each
+ * sub-step whether any particle is due.  Errors: those of
  * p3m_sr_force, plus EINVAL for dt <= 0, n_steps outside [1, 64], max_rung
  * outside [0, 7], unknown flags, eps < 0, eps or eta not positive without
  * fixed rungs, fixed rungs above max_rung, NULL vel or rung.

@@ -141,6 +141,8 @@ double sig_distance(const int *a, const int *b) {
 // A cached layout is reused for a particle set whose signature is this close.
 constexpr double kSigMatch = 0.05;
 
+constexpr int kTotSlots = 4;   // totals in pinned memory
+
 }  // namespace
 
 struct p3m_sr_context {
@@ -178,7 +180,10 @@ struct p3m_sr_context {
     // start, pairs start, pairs end, end, sort end
     hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     hipEvent_t tot_ev = nullptr;   // after the totals of a call reach host memory
-    int *host_tot = nullptr;   // pinned: receivers, clusters, items of the current call
+    // pinned: receivers, clusters and items of the current call, four ints per
+    // slot; calls write slot 0, the sub-steps of a KDK step in turn all of them
+    int *host_tot = nullptr;
+    int tot_slot = 0;
     // long-range PM workspace and timing
     DevBuf pm_real, pm_spec, pm_tab, pm_key, pm_rank, pm_bins, pm_rec, pm_nkey, pm_perm, pm_bsum,
         p3m_lr, tune_w, tune_sig;
@@ -194,6 +199,7 @@ struct p3m_sr_context {
     hipEvent_t lr_ev[9] = {};   // start, sort, deposit, x, y, z, y inverse, x inverse, readout
     // KDK step workspace
     DevBuf kdk_acc, kdk_lr, kdk_tq, kdk_tnext, kdk_due, kdk_scal;
+    hipEvent_t kdk_ev[kTotSlots] = {};   // after a sub-step's force call, by its slot
     p3m_kdk_stats kdk_stats{};
 };
 
@@ -853,12 +859,12 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
         pa.stall = stall;
         pa.n_clusters = n_clusters;
         pa.n_items = n_items;
-        pa.host_tot = h->host_tot;
+        pa.host_tot = h->host_tot + 4 * h->tot_slot;
         P3M_HIP(launch_plan(pa, g, s));
         while (wait_count) {
             P3M_HIP(hipEventRecord(h->tot_ev, s));
             P3M_HIP(hipEventSynchronize(h->tot_ev));
-            const size_t count = (size_t)std::max(h->host_tot[2], 1);
+            const size_t count = (size_t)std::max(pa.host_tot[2], 1);
             const size_t used = w.used;
             rc = take(h, w, w.items, sizeof(Item) * count, s);
             if (!rc && det)
@@ -1045,7 +1051,7 @@ int p3m_sr_create(p3m_sr_handle *out, int device) {
     h->device = device;
     // fine-grained (coherent) pinned memory: the kernel's stores reach the
     // host without a cache flush, and are read after the stream synchronises
-    if (hipHostMalloc((void **)&h->host_tot, 4 * sizeof(int),
+    if (hipHostMalloc((void **)&h->host_tot, kTotSlots * 4 * sizeof(int),
                       hipHostMallocMapped | hipHostMallocCoherent) !=
         hipSuccess) {
         (void)hipGetLastError();
@@ -1104,6 +1110,8 @@ int p3m_sr_destroy(p3m_sr_handle h) {
         if (e) (void)hipEventDestroy(e);
     if (h->tot_ev) (void)hipEventDestroy(h->tot_ev);
     for (hipEvent_t e : h->lr_ev)
+        if (e) (void)hipEventDestroy(e);
+    for (hipEvent_t e : h->kdk_ev)
         if (e) (void)hipEventDestroy(e);
     if (h->host_tot) (void)hipHostFree(h->host_tot);
     if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
@@ -1648,9 +1656,10 @@ int p3m_sr_get_stats(p3m_sr_handle h, p3m_sr_stats *out) {
         // the totals of the latest run of the call (the plan writes them to
         // pinned memory; a graph replay of the call writes them again)
         P3M_HIP(hipStreamSynchronize(h->last_stream));
-        st.receivers = h->host_tot[0];
-        st.clusters = h->host_tot[1];
-        st.items = h->host_tot[2];
+        const int *tot = h->host_tot + 4 * h->tot_slot;
+        st.receivers = tot[0];
+        st.clusters = tot[1];
+        st.items = tot[2];
     }
     if (h->last_counters && st.n > 0) {
         Counters cp[kCounterCopies * kCounterStride];
@@ -1787,10 +1796,13 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
     uint8_t *due = (uint8_t *)h->kdk_due.p;
 
     // the call's softening is eps for both the forces and eq. rung
-    struct EpsGuard {
+    struct CallGuard {
         p3m_sr_context *h;
         double saved;
-        ~EpsGuard() { h->eps = saved; }
+        ~CallGuard() {
+            h->eps = saved;
+            h->tot_slot = 0;
+        }
     } guard{h, h->eps};
     h->eps = eps;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1849,14 +1861,28 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
     // Every sub-step has due particles unless rung L has emptied by down-jumps.
     // With a wave's worth of particles on it (or fixed rungs, which keep
     // theirs) the sub-steps are queued without asking: a wait per sub-step
-    // leaves the GPU idle for 45 to 60 us, and a force call without receivers,
-    // should one occur, costs no more than the drift and the wait did.
-    const bool ask = !fixed && census[L] < kWave;
+    // leaves the GPU idle for 45 to 60 us.  A force call without receivers
+    // takes 38 us for 8192 particles and 58 for 131072, but 97 for 2^19 and
+    // 243 for 2^21.  So in sets above kWatchFrom the host looks, before it
+    // queues a sub-step, at the receivers of the one two before the last
+    // (whose wait leaves the last on the GPU), and asks from the first empty
+    // one on.
+    constexpr int kWatchFrom = 1 << 17;
+    bool ask = !fixed && census[L] < kWave;
+    const bool watch = !fixed && !ask && np > kWatchFrom;
+    auto slot_of = [&](int t) { return ((k.period - t) / 2) % kTotSlots; };   // the last in slot 0
+    if (watch)
+        for (hipEvent_t &e : h->kdk_ev)
+            if (!e) P3M_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     const int substeps = k.period / 2;
     KdkAdvance adv{pos, vel, acc, due, rung, t_q, t_next, np, tau, box, h->last_counters, pairs};
     P3M_HIP(launch_kdk_advance(adv, false, true, 0, k, scal + kCounts, s));
     for (int t = 2; t <= k.period; t += 2) {
         int n_due = 1;
+        if (watch && !ask && t >= 6) {
+            P3M_HIP(hipEventSynchronize(h->kdk_ev[slot_of(t - 4)]));
+            ask = h->host_tot[4 * slot_of(t - 4)] == 0;
+        }
         if (ask) {
             P3M_HIP(hipMemcpyAsync(&n_due, scal + kCounts + t / 2 - 1, sizeof(int),
                                    hipMemcpyDeviceToHost, s));
@@ -1865,7 +1891,9 @@ int p3m_kdk_step(p3m_sr_handle h, double *pos, double *vel, const double *mass, 
         if (n_due > 0) {
             r.sel = due;
             r.sel_kind = SEL_MASK;
+            h->tot_slot = slot_of(t);
             if ((rc = run(h, r, h->work))) return rc;
+            if (watch) P3M_HIP(hipEventRecord(h->kdk_ev[slot_of(t)], s));
             adv.counters = h->last_counters;
         }
         const bool last = t == k.period, lr = n_grid && t % span0 == 0;
