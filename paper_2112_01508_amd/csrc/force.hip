@@ -505,13 +505,13 @@ struct ItemCtx {
 // pair loop.
 template <class Body>
 struct DirectVisit {
+    static constexpr bool kHalf = false;   // the whole stencil
     Body &body;
     const ItemCtx &c;
     const PairArgs &a;
     WaveCounts &wc;
     bool shifted = false;
     double shx = 0.0, shy = 0.0, shz = 0.0;
-    __device__ __forceinline__ int first(int j0) const { return j0; }
     __device__ __forceinline__ void tile(int, int, bool sh, double x, double y, double z) {
         shifted = sh;
         shx = x;
@@ -541,6 +541,7 @@ struct DirectVisit {
 // copies of the cluster share the wave.
 template <int G, int CAP, class Body>
 struct ScreenVisit {
+    static constexpr bool kHalf = false;
     static constexpr bool W = Body::kNeedW;
     Body &body;
     const ItemCtx &c;
@@ -607,7 +608,6 @@ struct ScreenVisit {
         fill = 0;
         if (n_list > CAP - kWave) flush();   // keeps n_list <= CAP
     }
-    __device__ __forceinline__ int first(int j0) const { return j0; }
     __device__ __forceinline__ void tile(int, int img, bool, double x, double y, double z) {
         if (img != code) {
             screen_chunk();
@@ -722,10 +722,11 @@ __device__ __forceinline__ void walk_item(Visit &v, const Item &item, const Clus
                 const int ra = __builtin_ctzll(m);
                 const unsigned long long rest = ~(m >> ra);
                 const int rb = rest ? ra + __builtin_ctzll(rest) : kWave;   // run [ra, rb)
-                int j0 = v.first(__builtin_amdgcn_readlane(cst, ra));
+                int j0 = __builtin_amdgcn_readlane(cst, ra);
                 int j1 = __builtin_amdgcn_readlane(cen, rb - 1);
+                if constexpr (Visit::kHalf) j0 = v.first(j0);
                 if (split) {
-                    const long long len = max(j1 - j0, 0);
+                    const long long len = j1 - j0;
                     j1 = j0 + (int)(len * (part + 1) / parts);
                     j0 += (int)(len * part / parts);
                 }
@@ -782,8 +783,12 @@ __device__ inline ItemQueue item_queue(const PairArgs &a) {
     return ItemQueue{n, batch, (int)(gridDim.x / kXcds) * nw * batch};
 }
 
-__device__ inline int next_item(const PairArgs &a, const ItemQueue &iq, int lane, ItemCursor &q) {
+// HOLD: `held` is the launch's queue; else it is read again at each claim.
+template <bool HOLD>
+__device__ inline int next_item(const PairArgs &a, const ItemQueue &held, int lane,
+                                ItemCursor &q) {
     if (q.cur < q.end) return q.cur++;
+    const ItemQueue iq = HOLD ? held : item_queue(a);
     const int home = (int)(blockIdx.x % kXcds);
     if (q.victim < 0) {
         q.victim = 0;
@@ -911,8 +916,12 @@ void k_pairs(PairArgs a) {
     void *wlist = wlists[SCREEN && BWD ? threadIdx.x / kWave : 0];
     ItemCursor cursor;
     WaveCounts wc;
-    const ItemQueue iq = item_queue(a);
-    for (int it = next_item(a, iq, lane, cursor); it >= 0; it = next_item(a, iq, lane, cursor)) {
+    // the screened FP64 adjoint has no SGPRs left to hold the queue's values
+    // in (2^21 clustered, clusters of 8: 8.7 ms held, 8.4 read again per claim)
+    constexpr bool HOLD = !(MODE == BWD_F64 && SCREEN);
+    const ItemQueue iq = HOLD ? item_queue(a) : ItemQueue{};
+    for (int it = next_item<HOLD>(a, iq, lane, cursor); it >= 0;
+         it = next_item<HOLD>(a, iq, lane, cursor)) {
         const Item item = a.items[it];
         const Cluster cl = a.clusters[item.cluster];
         // receivers replicated over G lane groups; lanes past G*cnt are idle
@@ -1428,6 +1437,7 @@ __device__ __forceinline__ T rows_sum(T v) {
 
 template <int R, bool UNIT, int KIND>
 struct MutualVisit {
+    static constexpr bool kHalf = true;   // of its own tile the records after the cluster
     static constexpr bool BWD = kMutIsBwd<KIND>;
     static constexpr bool F64 = kMutIsF64<KIND>;
     using Lane = typename MutPick<F64, MutualLane64, MutualLane>::type;
@@ -1735,7 +1745,8 @@ void k_pairs_mutual(PairArgs a) {
     ItemCursor cursor;
     MutualTally tally;
     const ItemQueue iq = item_queue(a);
-    for (int it = next_item(a, iq, lane, cursor); it >= 0; it = next_item(a, iq, lane, cursor)) {
+    for (int it = next_item<true>(a, iq, lane, cursor); it >= 0;
+         it = next_item<true>(a, iq, lane, cursor)) {
         const Item item = a.items[it];
         const Cluster cl = a.clusters[item.cluster];
         const int cnt = __builtin_amdgcn_readfirstlane(cl.count);
