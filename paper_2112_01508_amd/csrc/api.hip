@@ -592,6 +592,21 @@ bool output_over_input(const Request &r) {
            over(r.sel, n) || over(r.grad_acc, sizeof(double) * 3 * n);
 }
 
+// What a configuration leaves open of a call that it has walk the suppliers
+// directly (screen 0).  Large sets take clusters of 64: a full one reads its
+// suppliers through the scalar unit (forward, 2^21 clustered, FP32: 3.75 ms, of
+// 32 5.25; FP64 5.6, of 16 6.2; 2^17: 0.269 and 0.278; FP64 adjoint, 2^21: 10.5
+// and 11.4, but 2^19 1.63 and 1.56).  Masked receivers are too sparse for that
+// (2.0 ms, of 8 1.7).  Finer subtiles make many runs of a walk, which favours
+// full clusters in both (from 3 per dimension; masked 2.5 and 2.6), and items
+// of 1024 (2 per dimension: 3.74 ms, of 4096 3.94).
+void direct_layout(Layout &def, int64_t n, int ns, bool backward, int sel_kind) {
+    const bool masked = !backward && sel_kind == SEL_MASK;
+    const int64_t from = backward && ns < 3 ? 3 << 18 : 1 << 17;
+    if (n >= from && (!masked || ns >= 3)) def.csize = 64;
+    if (ns >= 2) def.target = std::min(def.target, 1024);
+}
+
 int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     hipStream_t s = r.stream;
     const int n = (int)r.n;
@@ -649,9 +664,10 @@ int run(p3m_sr_context *h, const Request &r, SrWork &w) {
     if (r.force_screen > 0) screen = r.force_screen - 1;
     // the fixed workspace holds the mutual kernel's sums beside everything
     // else it held for a call up to half its particle limit
-    const Layout def = default_layout(r.n, nt, fp32, r.backward, r.sel_kind,
+    Layout def = default_layout(r.n, nt, fp32, r.backward, r.sel_kind,
                                       mutual_ok && !(w.base && r.n > kNoAllocMaxN / 2));
     ns = pick_subtiles(nt, ns > 0 ? ns : def.ns);
+    if (screen == 0) direct_layout(def, r.n, ns, r.backward, r.sel_kind);
     if (target <= 0) target = def.target;
     if (!valid_csize(csize)) csize = screen == kScreenMutual ? std::max(def.csize, 16) : def.csize;
     if (screen < 0) screen = def.screen == kScreenMutual && csize < 16 ? 1 : def.screen;
