@@ -380,6 +380,9 @@ int p3m_sr_set_softening(p3m_sr_handle h, double eps);
  *   - layout screen 2 runs as screen 1, or as the layout the autotuner kept
  *     beside an autotuned screen 2 (the kernel that evaluates each pair for
  *     both partners adds its reactions with atomics).
+ * The order is that of the call's layout; a call whose workspace cannot hold
+ * the slots of dense tiles split into several items takes them unsplit, in
+ * the order of that plan.
  * The accepted pairs are the same in both modes and the forces differ only
  * by the rounding of the summation order.  The sort and the partial slots
  * cost time and workspace (24 B per particle, 24 B per item and receiver
@@ -433,10 +436,9 @@ int p3m_sr_get_stats(p3m_sr_handle h, p3m_sr_stats *out);
  * n_grid^2 + n_grid^3 / 128 + 48 n bytes (grids, counts of the 8^3-node bins,
  * particles sorted by bin).  The deposit adds with FP64 atomics (in LDS, and
  * in HBM for bins of more than 2048 particles), so results can differ between
- * runs in
- * the last bits.  Errors: EINVAL for n < 0, box or x_s not positive and
- * finite, n_grid outside the supported set, NULL pos/acc_out with n > 0, or
- * pointers not 8-byte aligned; EUNSUPPORTED for n > 2^31 - 16; ENOMEM; EHIP.
+ * runs in the last bits.  Errors: EINVAL for n < 0, box or x_s not positive
+ * and finite, n_grid outside the supported set, NULL pos/acc_out with n > 0,
+ * or pointers not 8-byte aligned; EUNSUPPORTED for n > 2^31 - 16; ENOMEM; EHIP.
  */
 int p3m_lr_force(p3m_sr_handle h, const double *pos, const double *mass,
                  const uint8_t *active, int64_t n, double box, int n_grid, double x_s,

@@ -538,11 +538,12 @@ constexpr double kBsplinePerPlummer = 2.8;
 // clusters, one subtile per tile (finer ones cost cull entries and drop no
 // supplier that the screen would not; 1 to 5 % slower at every size measured).
 //   - Every particle a receiver, FP64: each pair once for both partners,
-//     clusters of 16, from 8192 particles on (2^21 clustered: 3.56 ms per call
-//     against 4.20 ms screened and 5.94 ms for 64-receiver clusters that walk
-//     their suppliers directly; 32768: 0.083 / 0.092 / 0.19 ms).  Below that
-//     the extra launch that writes its sums out costs as much as it saves
-//     (4096: 0.052 against 0.050 ms).
+//     clusters of 16, from 8192 particles on (2^21 clustered: 3.51 ms per call
+//     against 4.46 ms screened and 5.6 ms for 64-receiver clusters that walk
+//     their suppliers directly; 32768: 0.080 / 0.109 / 0.17 ms).  It forms the
+//     separations as the ordered kernels do.  Below that the extra launch that
+//     writes its sums out costs as much as it saves (4096: 0.052 against
+//     0.050 ms).
 //   - FP32 stays on the ordered kernels, which take the separation in FP64;
 //     clusters of 32 (2^21: 2.57 ms, of 16 2.63 ms, of 64 directly 4.19 ms).
 //   - The FP32 adjoint keeps 64-receiver clusters that walk their suppliers

@@ -1312,7 +1312,8 @@ struct EntryImage {
 // itself.  (From offsets to the cluster's centre, as the FP32 kinds take it,
 // the separation of a pair differed by up to 1e-13 of itself: uniform 32768,
 // largest error of a particle's force over the sum of its terms 2.2e-14, now
-// as the ordered kernel's 7e-16.)
+// as the ordered kernel's 7e-16.  The pairs that had to be redone are gone
+// too: 2^21 clustered 3.46 -> 3.25 ms per call.)
 template <int S, bool UNIT, bool SELF, bool BWD, bool SOFT, bool IMG>
 __device__ __forceinline__ void mutual_step64(MutualLane64 &m, const double4 &e,
                                               const double4 &ew, const EntryImage &img,

@@ -7,9 +7,11 @@
 // span(l) = 2^(L+1-l) units.  Each particle carries the time of its
 // momentum (t_q) and of its next kick (t_next); a kick at time t brings the
 // momentum to t + span(rung) / 2, or to the period's end at the last kick.
-// The host loop (api.hip) drifts, marks the particles due at t, evaluates the
-// short-range force with them as receivers and calls k_kdk_kick; the
-// long-range force is added to everyone whenever rung 0 kicks.
+// The host loop (api.hip) evaluates the short-range force with the particles
+// due at t as receivers and calls k_kdk_advance, which kicks them, drifts
+// everyone over tau and marks and counts the particles due at t + 2; where the
+// long-range force kicks everyone (whenever rung 0 kicks), between the short
+// kick and the drift, those two are calls of their own.
 #include <hip/hip_runtime.h>
 
 #include "p3msr_internal.hpp"

@@ -85,9 +85,9 @@ __device__ inline int block_exclusive_scan(int v, int *lds, int *total) {
 // Cell key and rank inside the cell of every particle.  n_scan != 0 (at most
 // kKeysScan cells): the block that finishes last scans the counts too, in place
 // (cell_count[n_scan] = n), which saves the launch of one to eight blocks (a
-// call on 4096 particles 46.6 -> 43.1 us, on 32768 73.6 -> 69.8 us).  Every block has its atomics' results before it
-// draws from *done (zeroed before the launch), and the last one reads the
-// counts with device-scope loads.
+// call on 4096 particles 46.6 -> 43.1 us, on 32768 73.6 -> 69.8 us).  Every
+// block has its atomics' results before it draws from *done (zeroed before the
+// launch), and the last one reads the counts with device-scope loads.
 constexpr int kKeysScan = 4 * kKeysThreads;
 
 template <int PPT>
